@@ -162,6 +162,10 @@ struct gmres_plan_s {
     double* part = nullptr;
     double *h1, *h2, *coef1, *coef2, *H, *Hraw, *cs, *sn, *g, *vscale, *sigma, *sigma0, *scal;
     double *cc = nullptr, *lag = nullptr;
+    // rendezvous words, partial sums and column maps of the gang launches
+    unsigned *gang_flags = nullptr, *gang_bmap = nullptr;
+    double *gang_part = nullptr, *gang_tpart = nullptr;
+    char* gang_args = nullptr;
     double *tpart = nullptr, *s_step = nullptr, *s_res = nullptr;
     Ctrl* ctrl = nullptr;
     Ctrl* ctrl_h = nullptr;             // pinned, 2 snapshots
@@ -304,6 +308,18 @@ int64_t hist_entries(const gmres_opts& o) {
     int64_t h = o.max_iters;
     if (o.precision != GMRES_FP64) h += (int64_t)std::max(o.max_refine, 0) * std::max<int64_t>(o.inner_max_iters, 0);
     return std::min<int64_t>(std::max<int64_t>(h, 1), int64_t(1) << 24);
+}
+
+void carve_gang(gmres_plan_s* p, Arena& A) {
+    int64_t rmax = 0;
+    for (int s = 0; s < p->nsys; ++s) rmax = std::max(rmax, p->zcol_off[s + 1] - p->zcol_off[s]);
+    p->gang_flags = A.take_n<unsigned>(kGangWG * kGangFlagWords);
+    p->gang_args = A.take_n<char>((int64_t)gang_args_bytes());
+    p->gang_part = A.take_n<double>(3 * (int64_t)gang_ps(p->o.m + 2) * kGangWG);
+    if (rmax > 0) {
+        p->gang_bmap = A.take_n<unsigned>(8 * kGangWG);
+        p->gang_tpart = A.take_n<double>(2 * (int64_t)gang_ps((int)rmax) * kGangWG);
+    }
 }
 
 void carve_krylov(gmres_plan_s* p, Arena& A) {
@@ -455,7 +471,10 @@ void carve_phase1(gmres_plan_s* p, Arena& A) {
         p->tsell_off = A.take_n<int>(nsl + 1);
         p->tsell_perm = A.take_n<int>(n);
     }
-    if (nsys == 1) carve_krylov(p, A);
+    if (nsys == 1) {
+        carve_krylov(p, A);
+        carve_gang(p, A);
+    }
     if (p->o.m <= 64) carve_batched(p, A);
 }
 
@@ -515,6 +534,7 @@ Layout layout_of(const gmres_plan_s* q, bool counted) {
     s->R = q->R;
     s->need_adjoint = q->need_adjoint;
     s->e_off_h = q->e_off_h;
+    s->zcol_off = q->zcol_off;
     s->NB = q->NB;
     s->CH = q->CH;
     Arena A;
@@ -969,6 +989,133 @@ gmres_status run_engine(gmres_plan_s* p, int op, int prec, const void* b, double
     return engine_end(r, out);
 }
 
+// Launch shape of a gang solve (gang.hip) for one engine, or K = 0 where the
+// kernel-per-phase engine runs: an explicit SpMV, grid or orthogonalisation
+// choice, kernel timing, no sliced-ELL copy, adaptive deflation, or a size
+// past the lines below.  256 rows a workgroup (a wavefront per SIMD) until
+// every compute unit has one.  Measured, us per step, gang / engine:
+//   FP64, 64 indicators: 66,049 rows, m = 50: 19.5 / 46; 263,169, m = 30:
+//   38 / 62; 361,201, m = 50 (589 KB of basis a workgroup): 58 / 72, m = 80
+//   (942 KB): 91 / 88; 491,401 (four rows a thread, spills), m = 30: 69 / 72,
+//   m = 50: 91 / 83.
+//   FP32 basis: 491,401 rows, m = 50: 49 / 63, m = 80 (635 KB): 65 / 72;
+//   FP16 basis, m = 50: 41 / 55.
+// Hence the limits of 700 KB of basis and of three (FP64) or four row slots.
+struct GangShape {
+    int K = 0, rpt = 0, vcap = 0, ecap = 0;
+    bool w9 = false;
+};
+
+GangShape gang_shape(const gmres_plan_s* p, int op, int prec) {
+    GangShape g;
+    const bool sell = op ? p->tsell_col != nullptr : p->sell_col != nullptr;
+    if (p->nsys != 1 || p->o.ortho != 1 || p->adapt.rmax > 0 || p->timer.period > 0 || !sell ||
+        (p->o.spmv_lanes != 0 && p->o.spmv_lanes != kSell) || p->o.num_blocks > 0)
+        return g;
+    int cus = 0, lds_max = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess ||
+        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, p->device) != hipSuccess)
+        return g;
+    const int kmax = std::min(cus, kGangWG);
+    const int64_t n = p->n;
+    int64_t rw = std::max<int64_t>(256, (n + kmax - 1) / kmax);
+    rw = (rw + 63) & ~int64_t(63);
+    const int vb = prec == kPrecF64 ? 8 : prec == kPrecF32 ? 4 : 2;
+    const int64_t full = rw * p->o.m * vb;
+    if (rw > (prec == kPrecF64 ? 3 : 4) * kGangRows || full > 700 * 1024) return g;
+    g.ecap = (int)std::min<int64_t>(8 * (int64_t)p->R * p->R, 16384);
+    const size_t fixed = gang_lds_fixed(p->o.m, prec) + (size_t)g.ecap;
+    if (fixed >= (size_t)lds_max) return g;
+    g.vcap = (int)std::min<int64_t>(full, (int64_t)lds_max - (int64_t)fixed);
+    g.K = (int)((n + rw - 1) / rw);
+    g.rpt = (int)((rw + kGangRows - 1) / kGangRows);
+    g.w9 = (op ? p->tsell_wmax : p->sell_wmax) <= 9;
+    return g;
+}
+
+// The operator, deflation data and shared buffers of a gang launch.
+void gang_args(gmres_plan_s* p, int op, int prec, GangHot& h, GangArgs& a) {
+    const EngineArgs e = make_args(p, op, prec);
+    h.m = e.m;
+    h.n = e.n;
+    h.R = h.Rmax = e.R;
+    h.trans = e.trans;
+    h.sell_off = e.sell_off;
+    h.perm = e.sell_perm;
+    h.wuni = e.sell_wuni;
+    h.sell_col = e.sell_col;
+    h.sell_val = e.sell_val;
+    h.Einv = e.Einv;
+    h.w = e.w;
+    h.V = e.V;
+    h.ldv = e.ldv;
+    h.flags = p->gang_flags;
+    h.part = p->gang_part;
+    h.tpart = p->gang_tpart;
+    a.st = p->st;
+    a.nscale = e.nscale;
+    a.zc1 = e.zc1;
+    a.zv1 = e.zv1;
+    a.zrp = e.zrp;
+    a.zci = e.zci;
+    a.zv = e.zv;
+    a.az2c = e.azc1;
+    a.az2v = e.azv1;
+    a.azrp = e.azrp;
+    a.azci = e.azci;
+    a.azv = e.azv;
+    a.xh = e.xh;
+    a.bmap = p->gang_bmap;
+    a.ctrl = e.ctrl;
+    a.abortw = reinterpret_cast<unsigned*>(&e.ctrl->pad32);
+    a.hist = e.hist;
+    a.hist_cap = e.hist_cap;
+    a.hist_base = p->hist_pos;
+    a.cyc_k = e.cyc_k;
+    a.cyc_cap = e.cyc_cap;
+}
+
+// Runs a whole solve of one engine from p->xh in gang launches; b: right-hand
+// side (type WT), xout: receives x_hat + Z E^{-1} Z^T r.  *ran = false when
+// the engine has no gang shape, a launch was refused or a rendezvous timed
+// out; xout may then hold anything.
+gmres_status run_gang(gmres_plan_s* p, int op, int prec, const void* b, double rtol, double r0_override,
+                      int64_t max_iters, bool trust_est, double* xout, Ctrl* out, bool* ran) {
+    *ran = false;
+    const GangShape g = gang_shape(p, op, prec);
+    if (g.K == 0) return GMRES_OK;
+    TraceRange tr_("gang solve");
+    GangHot h{};
+    GangArgs a{};
+    gang_args(p, op, prec, h, a);
+    h.K = g.K;
+    h.vcap = g.vcap;
+    h.ecap = g.ecap;
+    a.trust_est = trust_est ? 1 : 0;
+    a.max_iters = max_iters;
+    a.rtol = rtol;
+    a.r0_override = r0_override;
+    a.b = b;
+    a.xout = xout;
+    // A launch ends after about this many steps and the next one resumes.
+    a.max_cycles = std::max(1, 8192 / p->o.m);
+    // The basis buffer may hold this precision's columns: an engine of another
+    // one clears it first.
+    if (p->last_prec != prec) p->last_prec = -1;
+    for (;;) {
+        if (!launch_gang(h, a, p->gang_args, prec, g.rpt, g.w9, g.K, 0)) return GMRES_OK;
+        HIP_OK(hipMemcpyAsync(&p->ctrl_h[0], p->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, p->st));
+        HIP_OK(hipStreamSynchronize(p->st));
+        *out = p->ctrl_h[0];
+        if (out->pad32 != 0) return GMRES_OK;
+        if (out->done) break;
+        a.resume = 1;
+    }
+    p->hist_pos += out->its;
+    *ran = true;
+    return GMRES_OK;
+}
+
 // ||b - A x|| in FP64 (scratch: p->w, partial slot of p->part).
 void spmv_f64(gmres_plan_s* p, int L, int NB, const double* x, double* y) {
     if (L == kSell)
@@ -1011,7 +1158,7 @@ gmres_status debug_checks(gmres_plan_s* p) {
 #ifdef GMRES_DEBUG
     HIP_OK(hipStreamSynchronize(p->st));
     const unsigned int bits = dbg_take_krylov() | dbg_take_batched() | dbg_take_block() |
-                              dbg_take_setup() | dbg_take_adapt();
+                              dbg_take_setup() | dbg_take_adapt() | dbg_take_gang();
     if (bits) {
         char msg[96];
         std::snprintf(msg, sizeof msg, "device bounds check failed (bits 0x%x)", bits);
@@ -1035,13 +1182,26 @@ gmres_status leave(gmres_plan_s* p) {
 gmres_status solve_f64(gmres_plan_s* p, int op, const double* b, const double* x0, double* x,
                        double rtol, double r0_override, int64_t max_iters, gmres_info* info) {
     const int64_t n = p->n;
-    launch_copy(p->st, b, p->bws, n);
-    if (x0) launch_copy(p->st, x0, p->xh, n);
-    else launch_fill(p->st, p->xh, n, 0.0);
+    auto start_x = [&]() {
+        if (x0) launch_copy(p->st, x0, p->xh, n);
+        else launch_fill(p->st, p->xh, n, 0.0);
+    };
+    start_x();
     Ctrl c{};
-    if (op == 0 && p->adapt.rmax > 0) adapt_reset(p->st, p->adapt);   // U starts empty
-    CHECK(run_engine(p, op, kPrecF64, p->bws, rtol, r0_override, max_iters, &c));
-    launch_correct(p->st, p->NB, (int)n, p->zrp, p->zci, p->zv, p->s_res, p->R, p->xh, x);
+    bool ran = false;
+    // With a start vector (which x may be) the result passes through r64, so a
+    // repeat on the per-phase engine still finds x0.
+    double* xo = x0 ? p->r64 : x;
+    CHECK(run_gang(p, op, kPrecF64, b, rtol, r0_override, max_iters, false, xo, &c, &ran));
+    if (ran) {
+        if (xo != x) launch_copy(p->st, xo, x, n);
+    } else {
+        launch_copy(p->st, b, p->bws, n);
+        start_x();
+        if (op == 0 && p->adapt.rmax > 0) adapt_reset(p->st, p->adapt);   // U starts empty
+        CHECK(run_engine(p, op, kPrecF64, p->bws, rtol, r0_override, max_iters, &c));
+        launch_correct(p->st, p->NB, (int)n, p->zrp, p->zci, p->zv, p->s_res, p->R, p->xh, x);
+    }
     if (op == 0 && p->adapt.rmax > 0) {
         AdaptState as{};
         HIP_OK(hipMemcpyAsync(&as, p->adapt.st, sizeof(as), hipMemcpyDeviceToHost, p->st));
@@ -1128,8 +1288,13 @@ gmres_status solve_mixed(gmres_plan_s* p, const double* b, const double* x0, dou
         launch_scale_to_f32(p->st, p->NB, (int)n, p->r64, p->scal, reinterpret_cast<float*>(p->bws));
         launch_fill(p->st, p->xh, n, 0.0);
         Ctrl c{};
-        CHECK(run_engine(p, 0, prec, p->bws, inner, 0.0, o.inner_max_iters, &c, true));
-        launch_correct(p->st, p->NB, (int)n, p->zrp, p->zci, p->zv, p->s_res, p->R, p->xh, p->dvec);
+        bool ran = false;
+        CHECK(run_gang(p, 0, prec, p->bws, inner, 0.0, o.inner_max_iters, true, p->dvec, &c, &ran));
+        if (!ran) {
+            launch_fill(p->st, p->xh, n, 0.0);
+            CHECK(run_engine(p, 0, prec, p->bws, inner, 0.0, o.inner_max_iters, &c, true));
+            launch_correct(p->st, p->NB, (int)n, p->zrp, p->zci, p->zv, p->s_res, p->R, p->xh, p->dvec);
+        }
         info->iters += c.its;
         info->cycles += c.cycles;
         info->refinements = ref + 1;

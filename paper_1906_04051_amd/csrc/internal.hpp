@@ -285,6 +285,63 @@ inline int64_t block_slots_bound(int64_t n, int RB, int R, int64_t znnz) {
     return std::min<int64_t>(nblk * std::min<int64_t>(R, kBlockColsMax), znnz);
 }
 
+// gang.hip
+// One cooperative launch of gangs of workgroups (see gang.hip).  Single
+// system: row_off = nullptr, one gang of K workgroups; batch: wg_* give every
+// workgroup's gang (member, size, queue class) and each class its systems.
+// What the step loop reads goes by value, the rest lies in device memory.
+struct GangHot {
+    int m, n, R, K, Rmax;
+    int vcap, ecap;           // LDS bytes for the basis and for rows of E^{-1}
+    int trans, wuni;
+    const int *sell_off, *perm;
+    const short* sell_col;
+    const void* sell_val;
+    const double* Einv;
+    void *w, *V;
+    int64_t ldv;
+    unsigned* flags;          // shared between the workgroups
+    double *part, *tpart;
+};
+struct GangArgs {
+    hipStream_t st;
+    int resume, trust_est;
+    int max_cycles;           // cycles of this launch (a later launch resumes)
+    int64_t max_iters;
+    double rtol, r0_override, nscale;
+    const int *zc1, *zrp, *zci;
+    const double *zv1, *zv;
+    const int *az2c, *azrp, *azci;
+    const void *az2v, *azv;
+    const void* b;
+    double *xh, *xout;
+    unsigned *abortw, *bmap;
+    // single system: state and records
+    Ctrl* ctrl;
+    double* hist;
+    int64_t hist_cap, hist_base;
+    int* cyc_k;
+    int cyc_cap;
+    // batch
+    const int *wg_member, *wg_size, *wg_class, *cls_ptr, *order;
+    int *ticket, *next_sys;
+    const int64_t *row_off, *zcol_off, *e_off, *v_off, *w_off;
+    const double* x0;
+    int64_t* out_i;
+    double* out_d;
+};
+constexpr int kGangWG = 256;    // largest launch (one workgroup per compute unit)
+constexpr int kGangRows = 512;  // rows per workgroup and row slot (threads)
+size_t gang_lds_fixed(int m, int prec);   // LDS bytes beside ecap and vcap
+size_t gang_args_bytes();
+constexpr int kGangFlagWords = 32;   // words between the workgroups' flags (a cache line each)
+// Row stride (doubles) of a workgroup's partial sums: whole cache lines.
+__host__ __device__ constexpr int gang_ps(int cols) { return (cols + 15) & ~15; }
+// False when the launch was refused (the caller uses the per-phase engine).
+// args_d: gang_args_bytes() of device memory.
+bool launch_gang(const GangHot& h, const GangArgs& a, void* args_d, int prec, int rpt, bool w9, int nwg,
+                 int nticket);
+
 // batched.hip
 // Host-visible record of a system that left the batched launch for its
 // continuation plan: written before the flag, the flag last with a
@@ -412,5 +469,6 @@ unsigned int dbg_take_batched();
 unsigned int dbg_take_block();
 unsigned int dbg_take_setup();
 unsigned int dbg_take_adapt();
+unsigned int dbg_take_gang();
 
 }  // namespace gm
