@@ -166,6 +166,11 @@ struct gmres_plan_s {
     unsigned *gang_flags = nullptr, *gang_bmap = nullptr;
     double *gang_part = nullptr, *gang_tpart = nullptr;
     char* gang_args = nullptr;
+    // batch in gangs: workgroups of the launch (0: one workgroup a system),
+    // classes, LDS split; wg_member / wg_size / wg_class, class pointers,
+    // system order, then abort word, tickets and published system indices
+    int gang_nwg = 0, gang_ncls = 0, gang_vcap = 0, gang_ecap = 0;
+    int *gang_sched = nullptr, *gang_words = nullptr;
     double *tpart = nullptr, *s_step = nullptr, *s_res = nullptr;
     Ctrl* ctrl = nullptr;
     Ctrl* ctrl_h = nullptr;             // pinned, 2 snapshots
@@ -409,6 +414,11 @@ void carve_batched(gmres_plan_s* p, Arena& A) {
         }
     } else {
         p->bV = static_cast<double*>(p->V);
+    }
+    if (ns > 1) {
+        carve_gang(p, A);
+        p->gang_sched = A.take_n<int>(3 * kGangWG + kGangCls + 1 + ns);
+        p->gang_words = A.take_n<int>(1 + kGangCls + kGangWG);
     }
     p->bW = A.take_n<double>(3 * padded);
     p->d_w_off = A.take_n<int64_t>(ns);
@@ -1823,6 +1833,186 @@ static void drop_graphs(gmres_plan_s* p) {
         }
 }
 
+// Schedule of a batch in gangs: systems in classes by the gang size they need
+// (512 rows a workgroup, sizes rounded up to a step), every class with at
+// least one gang, further gangs to the class with the most steps left per
+// gang until the chip is full.  Steps grow like the square root of the rows
+// (mesh width).  Kept (gang_nwg > 0) where its estimate beats one workgroup
+// per system: a system-step takes about 18 ns a row there, with at most one
+// per compute unit in flight; in a gang about 6 us plus 30 ns for each row of
+// a workgroup (96 systems of 289 to 9,409 rows: 172 -> 26 ms; a chip-filling
+// batch stays where it was, its rows cost half as much without rendezvous).
+static gmres_status plan_batch_gangs(gmres_plan_s* p) {
+    p->gang_nwg = 0;
+    const int ns = p->nsys;
+    int cus = 0, lds_max = 0;
+    HIP_OK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+    HIP_OK(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, p->device));
+    if (!p->sell_col || p->sell_perm || p->o.batch_wg > 0 || p->o.batch_lanes > 0) return GMRES_OK;
+    static const int kSize[kGangCls] = {256, 192, 128, 96, 64, 48, 32, 24, 16, 12, 8, 6, 4, 3, 2, 1};
+    const int wgs = std::min(cus, kGangWG);
+    auto rows = [&](int s) { return p->row_off[s + 1] - p->row_off[s]; };
+    std::vector<std::vector<int>> in(kGangCls);
+    double old_max = 0, old_sum = 0;
+    int64_t rmax = 0;
+    for (int s = 0; s < ns; ++s) {
+        const double st = std::sqrt((double)rows(s)), t = 0.018 * (double)rows(s) * st;
+        old_max = std::max(old_max, t);
+        old_sum += t;
+        rmax = std::max(rmax, p->zcol_off[s + 1] - p->zcol_off[s]);
+        const int64_t need = (rows(s) + kGangRows - 1) / kGangRows;
+        int c = kGangCls - 1;
+        while (c >= 0 && kSize[c] < need) --c;
+        if (c < 0 || kSize[c] > wgs) return GMRES_OK;
+        in[c].push_back(s);
+    }
+    // Too many classes for one gang each: the one with the least work joins
+    // the next larger size.
+    for (;;) {
+        int sum = 0, least = -1;
+        double lw = 0;
+        bool larger = false;
+        for (int c = 0; c < kGangCls; ++c) {
+            if (in[c].empty()) continue;
+            sum += kSize[c];
+            double w = 0;
+            for (int s : in[c]) w += std::sqrt((double)rows(s));
+            if (larger && (least < 0 || w < lw)) {
+                least = c;
+                lw = w;
+            }
+            larger = true;
+        }
+        if (sum <= wgs || least < 0) break;
+        int up = least - 1;
+        while (in[up].empty()) --up;
+        in[up].insert(in[up].end(), in[least].begin(), in[least].end());
+        in[least].clear();
+    }
+    std::vector<int> size, ptr{0}, order;
+    std::vector<double> work;   // steps x time of a class
+    double new_max = 0;
+    int used = 0;
+    int64_t rw_max = 64;
+    for (int c = 0; c < kGangCls; ++c) {
+        if (in[c].empty()) continue;
+        std::stable_sort(in[c].begin(), in[c].end(), [&](int a, int b) { return rows(a) > rows(b); });
+        double w = 0;
+        for (int s : in[c]) {
+            const int64_t rw = ((rows(s) + kSize[c] - 1) / kSize[c] + 63) & ~int64_t(63);
+            const double t = (6.0 + 0.03 * (double)rw) * std::sqrt((double)rows(s));
+            w += t;
+            new_max = std::max(new_max, t);
+            rw_max = std::max(rw_max, rw);
+            order.push_back(s);
+        }
+        size.push_back(kSize[c]);
+        work.push_back(w);
+        ptr.push_back((int)order.size());
+        used += kSize[c];
+    }
+    const int nc = (int)size.size();
+    if (used > wgs) return GMRES_OK;
+    std::vector<int> gangs(nc, 1);
+    for (;;) {
+        int best = -1;
+        for (int c = 0; c < nc; ++c)
+            if (gangs[c] < ptr[c + 1] - ptr[c] && used + size[c] <= wgs &&
+                (best < 0 || work[c] / gangs[c] > work[best] / gangs[best]))
+                best = c;
+        if (best < 0) break;
+        ++gangs[best];
+        used += size[best];
+    }
+    double new_t = new_max;
+    for (int c = 0; c < nc; ++c) new_t = std::max(new_t, work[c] / gangs[c]);
+    if (new_t >= std::max(old_max, old_sum / wgs)) return GMRES_OK;
+    const int ecap = (int)std::min<int64_t>(8 * rmax * rmax, 16384);
+    const int64_t fixed = (int64_t)gang_lds_fixed(p->o.m, kPrecF64) + ecap;
+    if (fixed >= lds_max) return GMRES_OK;
+    std::vector<int> sched(3 * kGangWG + kGangCls + 1 + ns, 0);
+    int wg = 0;
+    for (int c = 0; c < nc; ++c)
+        for (int k = 0; k < gangs[c]; ++k)
+            for (int i = 0; i < size[c]; ++i, ++wg) {
+                sched[wg] = i;
+                sched[kGangWG + wg] = size[c];
+                sched[2 * kGangWG + wg] = c;
+            }
+    std::copy(ptr.begin(), ptr.end(), sched.begin() + 3 * kGangWG);
+    std::copy(order.begin(), order.end(), sched.begin() + 3 * kGangWG + kGangCls + 1);
+    HIP_OK(hipMemcpy(p->gang_sched, sched.data(), sched.size() * sizeof(int), hipMemcpyHostToDevice));
+    p->gang_ecap = ecap;
+    p->gang_vcap = (int)std::min<int64_t>(rw_max * p->o.m * 8, lds_max - fixed);
+    p->gang_ncls = nc;
+    p->gang_nwg = wg;
+    return GMRES_OK;
+}
+
+// The batch as gangs in one cooperative launch; *ran = false where it has no
+// schedule, the launch was refused or a rendezvous timed out.
+static gmres_status run_batch_gangs(gmres_plan_s* p, const double* b, const double* x0, double* x, bool* ran) {
+    *ran = false;
+    if (p->gang_nwg == 0 || p->ncont > 0) return GMRES_OK;
+    GangHot h{};
+    h.m = p->o.m;
+    h.ecap = p->gang_ecap;
+    h.vcap = p->gang_vcap;
+    for (int s = 0; s < p->nsys; ++s) h.Rmax = std::max(h.Rmax, (int)(p->zcol_off[s + 1] - p->zcol_off[s]));
+    h.sell_off = p->sell_off;
+    h.wuni = p->sell_wuni;
+    h.sell_col = p->sell_col;
+    h.sell_val = p->sell_v64;
+    h.Einv = p->Einv;
+    h.w = p->bW;
+    h.V = p->bV;
+    h.flags = p->gang_flags;
+    h.part = p->gang_part;
+    h.tpart = p->gang_tpart;
+    GangArgs a{};
+    a.st = p->st;
+    a.max_cycles = INT32_MAX;
+    a.max_iters = p->o.max_iters;
+    a.rtol = p->o.rtol;
+    a.nscale = 1.0;
+    a.zc1 = p->zc1;
+    a.zv1 = p->zv1;
+    a.zrp = p->zrp;
+    a.zci = p->zci;
+    a.zv = p->zv;
+    a.az2c = p->azc1;
+    a.az2v = p->azv1;
+    a.azrp = p->azrp;
+    a.azci = p->azci;
+    a.azv = p->azv;
+    a.b = b;
+    a.xh = x;
+    a.x0 = x0;
+    a.bmap = p->gang_bmap;
+    a.abortw = reinterpret_cast<unsigned*>(p->gang_words);
+    a.ticket = p->gang_words + 1;
+    a.next_sys = p->gang_words + 1 + kGangCls;
+    a.ncls = p->gang_ncls;
+    a.wg_member = p->gang_sched;
+    a.wg_size = p->gang_sched + kGangWG;
+    a.wg_class = p->gang_sched + 2 * kGangWG;
+    a.cls_ptr = p->gang_sched + 3 * kGangWG;
+    a.order = p->gang_sched + 3 * kGangWG + kGangCls + 1;
+    a.row_off = p->d_row_off;
+    a.zcol_off = p->d_zcol_off;
+    a.e_off = p->d_e_off;
+    a.v_off = p->d_v_off;
+    a.w_off = p->d_w_off;
+    a.out_i = p->bout_i;
+    a.out_d = p->bout_d;
+    if (!launch_gang(h, a, p->gang_args, kPrecF64, 1, p->sell_wmax <= 9, p->gang_nwg, kGangCls)) return GMRES_OK;
+    int aborted = 0;
+    HIP_OK(hipMemcpyAsync(&aborted, p->gang_words, sizeof(int), hipMemcpyDeviceToHost, p->st));
+    HIP_OK(hipStreamSynchronize(p->st));
+    *ran = aborted == 0;
+    return GMRES_OK;
+}
+
 static gmres_status init_batched(gmres_plan_s* p) {
     const int ns = p->nsys;
     const int m = p->o.m;
@@ -1848,6 +2038,7 @@ static gmres_status init_batched(gmres_plan_s* p) {
     HIP_OK(hipMemcpy(p->border, order.data(), ns * sizeof(int), hipMemcpyHostToDevice));
     HIP_OK(hipMemcpy(p->d_v_off, voff.data(), ns * sizeof(int64_t), hipMemcpyHostToDevice));
     HIP_OK(hipMemcpy(p->d_w_off, woff.data(), ns * sizeof(int64_t), hipMemcpyHostToDevice));
+    if (ns > 1) CHECK(plan_batch_gangs(p));
     // Padding rows of the work vectors (and, for batches, of the basis) read as zero.
     HIP_OK(hipMemsetAsync(p->bW, 0, 3 * (size_t)(p->n + ns) * sizeof(double), p->st));
     if (ns > 1) {
@@ -2106,7 +2297,14 @@ gmres_status gmres_solve_batched(gmres_plan p, const double* b, const double* x0
     if (!p->bV) return fail(GMRES_EINVAL, "the batched solver supports m <= 64");
     const auto t0 = std::chrono::steady_clock::now();
     CHECK(enter(p));
-    CHECK(run_batched(p, b, x0, x, p->o.max_iters, p->batch_wg, p->batch_L));
+    bool ran = false;
+    const double* xs = x0;
+    if (p->gang_nwg > 0 && x0 == x) {   // the start vectors survive a repeat
+        launch_copy(p->st, x0, p->btune_x, p->n);
+        xs = p->btune_x;
+    }
+    CHECK(run_batch_gangs(p, b, xs, x, &ran));
+    if (!ran) CHECK(run_batched(p, b, xs, x, p->o.max_iters, p->batch_wg, p->batch_L));
     const int ns = p->nsys;
     double* nr = p->bout_d + 4 * (int64_t)ns;
     std::vector<int64_t> oi(3 * (size_t)ns);

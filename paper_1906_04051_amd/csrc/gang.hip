@@ -328,10 +328,12 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
         int c0 = 0;
         if constexpr (BATCH) {
             if (me == 0 && tid == 0) {
-                const int cls = a.wg_class[blockIdx.x];
-                const int t = atomicAdd(a.ticket + cls, 1);
-                const int q = a.cls_ptr[cls] + t;
-                const int s = q < a.cls_ptr[cls + 1] ? a.order[q] : -1;
+                // Own class first, then the classes of smaller gangs.
+                int s = -1;
+                for (int c = a.wg_class[blockIdx.x]; c < a.ncls && s < 0; ++c) {
+                    const int q = a.cls_ptr[c] + atomicAdd(a.ticket + c, 1);
+                    if (q < a.cls_ptr[c + 1]) s = a.order[q];
+                }
                 si[4] = s;
                 if (K > 1) st_ag((int*)a.next_sys + first, s);
             }

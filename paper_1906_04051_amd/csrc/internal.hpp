@@ -323,6 +323,7 @@ struct GangArgs {
     int* cyc_k;
     int cyc_cap;
     // batch
+    int ncls;
     const int *wg_member, *wg_size, *wg_class, *cls_ptr, *order;
     int *ticket, *next_sys;
     const int64_t *row_off, *zcol_off, *e_off, *v_off, *w_off;
@@ -331,6 +332,7 @@ struct GangArgs {
     double* out_d;
 };
 constexpr int kGangWG = 256;    // largest launch (one workgroup per compute unit)
+constexpr int kGangCls = 16;    // queue classes of a batch
 constexpr int kGangRows = 512;  // rows per workgroup and row slot (threads)
 size_t gang_lds_fixed(int m, int prec);   // LDS bytes beside ecap and vcap
 size_t gang_args_bytes();

@@ -115,3 +115,43 @@ def test_gang_converges_like_the_engine():
     z, info = plan.solve(torch.zeros_like(bad))
     assert info["iters"] == 0 and float(z.abs().max()) == 0.0
     plan.close()
+
+
+@pytest.mark.parametrize("lo,hi,ns,s,m,steps", [
+    (16, 40, 5, 2, 30, 60),      # one- to four-workgroup gangs
+    (24, 90, 6, 0, 64, 70),      # no deflation basis; basis beyond LDS
+    (16, 96, 40, 4, 30, 60),     # several systems a gang
+    (230, 256, 3, 4, 10, 25),    # gangs of 128 and more
+])
+def test_gang_batch_matches_one_workgroup_a_system(lo, hi, ns, s, m, steps):
+    from paper_1906_04051_amd import gmres as G
+    batch = W.make_batch(ns, lo, hi, s)
+    x0 = torch.from_numpy(np.random.default_rng(3).uniform(-1, 1, batch.b.size)).cuda()
+    res = []
+    for kw in (dict(), dict(batch_wg=256)):
+        plan, d = G.plan_for(batch, m=m, rtol=0.0, max_iters=steps, **kw)
+        x = x0.clone()
+        plan.solve_batched(d["b"], x0=x, out=x)
+        y, infos = plan.solve_batched(d["b"])
+        res.append((x.cpu().numpy(), y.cpu().numpy(), infos))
+        plan.close()
+    for i in range(ns):
+        a, b = (r[2][i] for r in res)
+        assert a["iters"] == b["iters"] == steps and a["cycles"] == b["cycles"]
+        r0, r1 = batch.row_off[i], batch.row_off[i + 1]
+        _close(res[0][0][r0:r1], res[1][0][r0:r1], f"system {i} from x0")
+        _close(res[0][1][r0:r1], res[1][1][r0:r1], f"system {i}")
+
+
+def test_gang_batch_to_tolerance():
+    from paper_1906_04051_amd import gmres as G
+    batch = W.make_batch(12, 16, 110, 4)
+    plan, d = G.plan_for(batch, m=30, rtol=1e-9, max_iters=20000)
+    x, infos = plan.solve_batched(d["b"])
+    for i, sysm in enumerate(batch.systems):
+        r0, r1 = batch.row_off[i], batch.row_off[i + 1]
+        xi = x[r0:r1].cpu().numpy()
+        res = np.linalg.norm(sysm.b - oracle.spmv(sysm.rowptr, sysm.colind, sysm.vals, xi))
+        assert infos[i]["status_name"] == "OK"
+        assert res <= 1.001e-9 * np.linalg.norm(sysm.b)
+    plan.close()
