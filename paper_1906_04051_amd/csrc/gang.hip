@@ -381,6 +381,8 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
 #pragma unroll
         for (int q = 0; q < RPT; ++q) gpos[q] = ok[q] ? p0 + pos[q] : min(p0, n - 1);
 
+        // Rows without A Z entries multiply s_0 by zero, listed or not.
+        for (int i = tid; i < kMaxR; i += kGN) sv[i] = 0.0;
         // Own rows of the exchanges start empty.
         slot = pslot = pcount = tslot = 0;
         tpend = -1;
@@ -766,7 +768,12 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
             } else {
                 const GM_GLB ST* bp = (const GM_GLB ST*)(Vg + gpos[q]);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = (ACC)bp[min(c + e, nv - 1) * ldv];
+                for (int e = 0; e < 8; ++e) {
+                    // A row that does not exist reads its neighbour's entry,
+                    // which may not have been written yet: dropped.
+                    const ACC t = (ACC)bp[min(c + e, nv - 1) * ldv];
+                    v[e] = ok[q] ? t : (ACC)0;
+                }
             }
         };
         // With three rows a thread their loads are kept apart: all in flight at
