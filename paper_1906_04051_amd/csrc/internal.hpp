@@ -168,7 +168,12 @@ struct EngineArgs {
     const AdaptArgs* adapt; // FP64 adaptive spectral deflation (nullptr: off)
     double* cc;             // lagged: coefficients (Hbar h2) of the next step, m + 1
     double* lag;            // lagged: h2_last, 1/hn, sigma
+    int paired;             // two Arnoldi steps per pair of sweeps
+    double* pst;            // its state (pair_state_doubles)
+    const double* sigma_a;  // power of two near 1 / max|A|
 };
+
+inline int64_t pair_state_doubles(int m) { return 5 * (int64_t)(m + 4) + 16; }
 
 // adapt.hip
 void adapt_reset(hipStream_t st, const AdaptArgs& a);
@@ -205,6 +210,8 @@ void launch_scale_to_f32(hipStream_t st, int NB, int n, const double* r, const d
                          float* out);
 void launch_axpy_norm(hipStream_t st, int NB, int n, const double* nrm2, const double* d, double* x);
 void launch_ctrl_reset(hipStream_t st, Ctrl* c, int64_t max_iters, int64_t hist_base);
+// *out = power of two near 1 / max|v|; part: cap doubles of scratch.
+void launch_value_scale(hipStream_t st, const double* v, int64_t n, double* part, int cap, double* out);
 void launch_fill(hipStream_t st, double* p, int64_t n, double v);
 void launch_copy(hipStream_t st, const double* a, double* b, int64_t n);
 

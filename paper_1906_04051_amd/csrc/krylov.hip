@@ -1607,6 +1607,569 @@ __global__ __launch_bounds__(kWG) void k_backsolve(int m, const double* __restri
     for (int i = threadIdx.x; i < k; i += kWG) coef[i] = yl[i] * vscale[i];
 }
 
+
+// --------------------------------------------- two Arnoldi steps per pair of sweeps
+// A pair advances the basis by two vectors from one set of sweeps, so the
+// basis is read twice per two steps instead of twice per step.  Pair p starts
+// with v_0 .. v_{nr-1} stored (nr = 2p - 1; v_0 alone for p = 0) and two
+// vectors a, b that have been projected once, with c2a = V^T a, c2b = V^T b
+// and the Cholesky factor r00, r01, r11 of what is left of their Gram matrix:
+//   u = P A (b / r11),  z = sigma P A u      (sigma: power of two near 1/max|A|).
+// First sweep (k_pair1): the second projection and normalisation
+//   v_{nr} = (a - V c2a) / r00,  v_{nr+1} = (b - V c2b - r01 v_{nr}) / r11,
+// and, with nv = nr + 2 columns, cu = V^T u, cz = V^T z, u.u, u.z, z.z.
+// Second sweep (k_pair2): the first projection of the next two vectors,
+//   a = u - V cu,  b = z - V cz - rho a,  rho = (u.z - cu.cz) / (u.u - cu.cu),
+// with the dots that correct them in the next pair.  So every vector, and the
+// pair among itself, is orthogonalised twice (block CGS2); b never depends on
+// a more than to first order when its factor is taken.  The columns of Hbar
+// follow from the Arnoldi relation P A V = V Hbar (eq. hessenberg):
+//   b / r11 = V f  and  u = V (cu + c2a) + r00 v_{nv},
+//   z = V (cz + rho c2a + c2b) + (rho r00 + r01) v_{nv} + r11 v_{nv+1}.
+// Both sweeps are bound by the basis they stream: at 4,198,401 rows and 41 to
+// 47 FP64 columns k_pair1 takes 221 us and k_pair2 194 us per two steps, where
+// the one-step sweeps took 2 x 208 and 2 x 186 us; with k_pdeflate (28 us) a
+// step of GMRES(50) went from 490 to 345 us, at 1,050,625 rows from 143 to 100.
+
+// w = y - (A Z) s for every row: the input of the pair's second product.
+template <typename WT, typename AZT, typename ACC>
+__global__ __launch_bounds__(kWG) void k_pdeflate(int n, const WT* __restrict__ y,
+                                                  const int* __restrict__ azrp,
+                                                  const int* __restrict__ azci,
+                                                  const AZT* __restrict__ azv,
+                                                  const int* __restrict__ azc2,
+                                                  const AZT* __restrict__ azv2,
+                                                  const double* __restrict__ s, int R,
+                                                  WT* __restrict__ w, const Ctrl* ctrl, int gate) {
+    constexpr int RT = 16 / (int)sizeof(WT);
+    __shared__ ACC s_l[kMaxR];
+    for (int a = threadIdx.x; a < R; a += kWG) s_l[a] = (ACC)s[a];
+    __syncthreads();
+    if (gated(ctrl, gate)) return;
+    const int64_t stride = (int64_t)gridDim.x * kWG * RT;
+    for (int64_t i0 = ((int64_t)blockIdx.x * kWG + threadIdx.x) * RT; i0 < n; i0 += stride) {
+        ACC u[RT];
+        load_tile<WT, RT, ACC>(y + i0, u);
+        deflate_tile<RT, AZT, ACC>(i0, azrp, azci, azv, azc2, azv2, s_l, u);
+        store_tile<WT, RT, ACC>(w + i0, u);
+    }
+}
+
+// Lanes per tile of the pair kernels: at most eight columns a lane, whose
+// tile, two coefficients and two sums take 64 to 96 registers.
+template <int J>
+struct LanesForPair {
+    static constexpr int value = J <= 8 ? 1 : (J <= 16 ? 2 : (J <= 32 ? 4 : (J <= 64 ? 8 : 16)));
+};
+
+// Workgroup sums of two accumulator sets (columns sub + q*T < nc) and of
+// extra values to part: set u at slots 0 .., set z at slots zoff .., then the
+// caller's NX extra sums at the slots in xs.  Fixed order.
+template <int JMAX, int T, int NX, typename ACC>
+__device__ __forceinline__ void store_pair_partials(const ACC (&au)[JMAX / T], const ACC (&az)[JMAX / T],
+                                                    const ACC (&ax)[NX], const int (&xs)[NX], int nc,
+                                                    int zoff, ACC (*red)[2 * JMAX + 8], double* part,
+                                                    int NB) {
+    constexpr int JT = JMAX / T;
+    const int wv = threadIdx.x / kWave, ln = threadIdx.x & (kWave - 1);
+    const int sub = ln & (T - 1);
+#pragma unroll
+    for (int q = 0; q < JT; ++q) {
+        if (q * T < nc) {
+            ACC t = au[q], v = az[q];
+#pragma unroll
+            for (int o = kWave / 2; o >= T; o >>= 1) {
+                t += __shfl_xor(t, o, kWave);
+                v += __shfl_xor(v, o, kWave);
+            }
+            const int k = sub + q * T;
+            if (ln < T && k < nc) {
+                red[wv][k] = t;
+                red[wv][JMAX + k] = v;
+            }
+        }
+    }
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+        const ACC t = wave_sum(ax[x]);
+        if (ln == 0) red[wv][2 * JMAX + x] = t;
+    }
+    __syncthreads();
+    for (int tk = threadIdx.x; tk < 2 * JMAX + NX; tk += kWG) {
+        int slot = -1;
+        if (tk < nc) slot = tk;
+        else if (tk >= JMAX && tk < JMAX + nc) slot = zoff + (tk - JMAX);
+        else if (tk >= 2 * JMAX) slot = xs[tk - 2 * JMAX];
+        if (slot < 0) continue;
+        ACC t = red[0][tk];
+#pragma unroll
+        for (int q = 1; q < kWG / kWave; ++q) t += red[q][tk];
+        part[(int64_t)slot * NB + blockIdx.x] = (double)t;
+    }
+}
+
+// First sweep of a pair (see above).  FIRST: only v_0 is stored and nothing
+// is pending (nr = 1, no new columns).  y holds sigma A u on entry, z on exit.
+// plag = {1/r00, r01, 1/r11}.
+template <int JMAX, int T, bool FIRST, typename VT, typename WT, typename AZT, typename ACC>
+__global__ __launch_bounds__(kWG) void k_pair1(int n, int64_t ldv, VT* __restrict__ V, int nr,
+                                               const WT* __restrict__ a, const WT* __restrict__ b,
+                                               const WT* __restrict__ u, WT* __restrict__ y,
+                                               const int* __restrict__ azrp,
+                                               const int* __restrict__ azci,
+                                               const AZT* __restrict__ azv,
+                                               const int* __restrict__ azc2,
+                                               const AZT* __restrict__ azv2,
+                                               const double* __restrict__ s, int R,
+                                               const double* __restrict__ ca,
+                                               const double* __restrict__ cb,
+                                               const double* __restrict__ plag, double stscale,
+                                               double* __restrict__ part, int NB, const Ctrl* ctrl,
+                                               int gate, int keep) {
+    constexpr int JT = JMAX / T;
+    constexpr int RT = 16 / sizeof(VT);
+    __shared__ ACC s_l[kMaxR];
+    __shared__ ACC ca_l[JMAX], cb_l[JMAX];
+    __shared__ ACC red[kWG / kWave][2 * JMAX + 8];
+    for (int k = threadIdx.x; k < R; k += kWG) s_l[k] = (ACC)s[k];
+    const int sub = threadIdx.x & (T - 1);
+    ACC car[JT], cbr[JT];
+    ACC ia = 0, r01 = 0, ib = 0;
+    if constexpr (!FIRST) {
+        for (int k = threadIdx.x; k < JMAX; k += kWG) cb_l[k] = k < nr ? (ACC)cb[k] : (ACC)0;
+        stage_coef<JMAX, T, ACC>(ca, nr, ca_l, sub, car);   // synchronises
+#pragma unroll
+        for (int q = 0; q < JT; ++q) cbr[q] = cb_l[sub + q * T];
+        ia = (ACC)plag[0];
+        r01 = (ACC)plag[1];
+        ib = (ACC)plag[2];
+    } else {
+        __syncthreads();
+    }
+    if (gated(ctrl, gate)) return;   // after the staging loads (uniform)
+    VT* __restrict__ va_out = V + nr * ldv;
+    VT* __restrict__ vb_out = va_out + ldv;
+    const ACC ss = (ACC)stscale;
+    ACC au[JT], az[JT];
+#pragma unroll
+    for (int q = 0; q < JT; ++q) au[q] = az[q] = 0;
+    ACC xu[4] = {0, 0, 0, 0};      // va.u, vb.u, va.z, vb.z
+    ACC gg[3] = {0, 0, 0};         // u.u, u.z, z.z
+    const int64_t stride = (int64_t)gridDim.x * (kWG / T) * RT;
+    // The first TS lanes of a tile group each own RS of its rows: they load
+    // the four vectors and the A Z copy, form the new columns and z and add
+    // to the sums; the group shares u and z for the dots (lane shuffles).
+    constexpr int TS = T < RT ? T : RT;
+    constexpr int RS = RT / TS;
+    const bool owner = sub < TS;
+    const int e0 = owner ? sub * RS : 0;
+    const int gbase = (threadIdx.x & (kWave - 1)) & ~(T - 1);
+    for (int64_t i0 = (((int64_t)blockIdx.x * kWG + threadIdx.x) / T) * RT; i0 < n; i0 += stride) {
+        uint4 raw[JT];
+        load_cols<JT, T, VT>(V, ldv, nr, sub, i0, keep, raw);
+        ACC av[RS], bv[RS], uv[RS], zv[RS];
+#pragma unroll
+        for (int r = 0; r < RS; ++r) av[r] = bv[r] = uv[r] = zv[r] = (ACC)0;
+        if (owner) {
+            if constexpr (!FIRST) {
+                load_rows<WT, RS, ACC>(a + i0 + e0, av);
+                load_rows<WT, RS, ACC>(b + i0 + e0, bv);
+            }
+            load_rows<WT, RS, ACC>(u + i0 + e0, uv);
+            load_rows<WT, RS, ACC>(y + i0 + e0, zv);
+            if (R > 0) {
+                deflate_tile<RS, AZT, ACC>(i0 + e0, azrp, azci, azv, azc2, azv2, s_l, zv);
+                store_rows<WT, RS, ACC>(y + i0 + e0, zv);
+            }
+        }
+        if constexpr (!FIRST) {
+            ACC a2o[RS], b2o[RS];
+#pragma unroll
+            for (int r = 0; r < RS; ++r) a2o[r] = b2o[r] = (ACC)0;
+#pragma unroll
+            for (int e = 0; e < RT; ++e) {
+                const ACC a2 = combine_row<JT, T, VT, ACC>(raw, car, e);
+                const ACC b2 = combine_row<JT, T, VT, ACC>(raw, cbr, e);
+                const bool mine = (e / RS) == sub;
+                a2o[e % RS] = mine ? a2 : a2o[e % RS];
+                b2o[e % RS] = mine ? b2 : b2o[e % RS];
+            }
+            ACC sa[RS], sb[RS];
+#pragma unroll
+            for (int r = 0; r < RS; ++r) {
+                const ACC va = (av[r] - a2o[r]) * ia;
+                const ACC vb = (bv[r] - b2o[r] - r01 * va) * ib;
+                VT t;
+                st_v(&t, va * ss);
+                sa[r] = (ACC)ld_f(&t);
+                st_v(&t, vb * ss);
+                sb[r] = (ACC)ld_f(&t);
+                if (owner) {
+                    xu[0] += sa[r] * uv[r];
+                    xu[1] += sb[r] * uv[r];
+                    xu[2] += sa[r] * zv[r];
+                    xu[3] += sb[r] * zv[r];
+                }
+            }
+            if (owner) {
+                store_rows<VT, RS, ACC>(va_out + i0 + e0, sa);
+                store_rows<VT, RS, ACC>(vb_out + i0 + e0, sb);
+            }
+        }
+        if (owner) {
+#pragma unroll
+            for (int r = 0; r < RS; ++r) {
+                gg[0] += uv[r] * uv[r];
+                gg[1] += uv[r] * zv[r];
+                gg[2] += zv[r] * zv[r];
+            }
+        }
+        ACC un[RT], zn[RT];
+        if constexpr (T > 1) {
+#pragma unroll
+            for (int e = 0; e < RT; ++e) {
+                un[e] = __shfl(uv[e % RS], gbase + e / RS, kWave);
+                zn[e] = __shfl(zv[e % RS], gbase + e / RS, kWave);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < RT; ++e) {
+                un[e] = uv[e];
+                zn[e] = zv[e];
+            }
+        }
+        accumulate_dots<JT, T, RT, VT, ACC>(raw, un, au);
+        accumulate_dots<JT, T, RT, VT, ACC>(raw, zn, az);
+    }
+    const int nv = FIRST ? nr : nr + 2;
+    if constexpr (FIRST) {
+        const int xs[3] = {2 * nv, 2 * nv + 1, 2 * nv + 2};
+        store_pair_partials<JMAX, T, 3, ACC>(au, az, gg, xs, nr, nv, red, part, NB);
+    } else {
+        const ACC ax[7] = {xu[0], xu[1], xu[2], xu[3], gg[0], gg[1], gg[2]};
+        const int xs[7] = {nr, nr + 1, nv + nr, nv + nr + 1, 2 * nv, 2 * nv + 1, 2 * nv + 2};
+        store_pair_partials<JMAX, T, 7, ACC>(au, az, ax, xs, nr, nv, red, part, NB);
+    }
+}
+
+// Second sweep of a pair over nv columns: a = u - V cu, b = z - V cz - rho a
+// and their dots; rho from the normalised sums hu, hz and gs = {u.u, u.z}.
+template <int JMAX, int T, typename VT, typename WT, typename ACC>
+__global__ __launch_bounds__(kWG) void k_pair2(int n, int64_t ldv, const VT* __restrict__ V, int nv,
+                                               const WT* __restrict__ u, const WT* __restrict__ z,
+                                               WT* __restrict__ a, WT* __restrict__ b,
+                                               const double* __restrict__ cu,
+                                               const double* __restrict__ cz,
+                                               const double* __restrict__ hu,
+                                               const double* __restrict__ hz,
+                                               const double* __restrict__ gs, double* __restrict__ rho_out,
+                                               double* __restrict__ part, int NB, const Ctrl* ctrl,
+                                               int gate, int keep) {
+    constexpr int JT = JMAX / T;
+    constexpr int RT = 16 / sizeof(VT);
+    __shared__ ACC cu_l[JMAX], cz_l[JMAX];
+    __shared__ ACC red[kWG / kWave][2 * JMAX + 8];
+    const int sub = threadIdx.x & (T - 1), ln = threadIdx.x & (kWave - 1);
+    // rho: every wave for itself (same order, same value).
+    double d1 = 0, d2 = 0;
+    for (int k = ln; k < nv; k += kWave) {
+        const double p = hu[k], q = hz[k];
+        d1 += p * q;
+        d2 += p * p;
+    }
+    const double uu = gs[0], uz = gs[1];
+    ACC cur[JT], czr[JT];
+    for (int k = threadIdx.x; k < JMAX; k += kWG) cz_l[k] = k < nv ? (ACC)cz[k] : (ACC)0;
+    stage_coef<JMAX, T, ACC>(cu, nv, cu_l, sub, cur);   // synchronises
+#pragma unroll
+    for (int q = 0; q < JT; ++q) czr[q] = cz_l[sub + q * T];
+    if (gated(ctrl, gate)) return;   // after the staging loads (uniform)
+    const double den = uu - wave_sum(d2), num = uz - wave_sum(d1);
+    const double rho_d = den > 0.0 ? num / den : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *rho_out = (double)(ACC)rho_d;
+    const ACC rho = (ACC)rho_d;
+    ACC au[JT], az[JT];
+#pragma unroll
+    for (int q = 0; q < JT; ++q) au[q] = az[q] = 0;
+    ACC gg[3] = {0, 0, 0};
+    const int64_t stride = (int64_t)gridDim.x * (kWG / T) * RT;
+    for (int64_t i0 = (((int64_t)blockIdx.x * kWG + threadIdx.x) / T) * RT; i0 < n; i0 += stride) {
+        uint4 raw[JT];
+        load_cols<JT, T, VT>(V, ldv, nv, sub, i0, keep, raw);
+        ACC av[RT], bv[RT];
+        load_tile<WT, RT, ACC>(u + i0, av);
+        load_tile<WT, RT, ACC>(z + i0, bv);
+#pragma unroll
+        for (int e = 0; e < RT; ++e) {
+            av[e] -= combine_row<JT, T, VT, ACC>(raw, cur, e);
+            bv[e] -= combine_row<JT, T, VT, ACC>(raw, czr, e) + rho * av[e];
+        }
+        if (sub == 0) {
+            store_tile<WT, RT, ACC>(a + i0, av);
+            store_tile<WT, RT, ACC>(b + i0, bv);
+#pragma unroll
+            for (int e = 0; e < RT; ++e) {
+                gg[0] += av[e] * av[e];
+                gg[1] += av[e] * bv[e];
+                gg[2] += bv[e] * bv[e];
+            }
+        }
+        accumulate_dots<JT, T, RT, VT, ACC>(raw, av, au);
+        accumulate_dots<JT, T, RT, VT, ACC>(raw, bv, az);
+    }
+    const int xs[3] = {2 * nv, 2 * nv + 1, 2 * nv + 2};
+    store_pair_partials<JMAX, T, 3, ACC>(au, az, gg, xs, nv, nv, red, part, NB);
+}
+
+// Sums of a pair sweep (one workgroup per slot, fixed order): h = vscale sum
+// against the normalised columns and coef = h vscale (coefficients of the
+// stored ones) for both vectors; the three Gram entries to gs.
+__global__ __launch_bounds__(kWG) void k_pair_finish(const double* __restrict__ part, int NB, int nv,
+                                                     const double* __restrict__ vscale,
+                                                     double* __restrict__ hu, double* __restrict__ hz,
+                                                     double* __restrict__ cu, double* __restrict__ cz,
+                                                     double* __restrict__ gs, const Ctrl* ctrl, int gate) {
+    __shared__ double red[kWG / kWave];
+    const int b = blockIdx.x;
+    double acc = 0;
+    for (int q = threadIdx.x; q < NB; q += kWG) acc += part[(int64_t)b * NB + q];
+    const int k = b < nv ? b : b - nv;
+    const double vs = (b < 2 * nv && threadIdx.x == 0) ? vscale[k] : 0.0;
+    if (gated(ctrl, gate)) return;
+    acc = block_sum(acc, red);
+    if (threadIdx.x != 0) return;
+    if (b < nv) {
+        hu[k] = vs * acc;
+        cu[k] = vs * acc * vs;
+    } else if (b < 2 * nv) {
+        hz[k] = vs * acc;
+        cz[k] = vs * acc * vs;
+    } else {
+        gs[b - 2 * nv] = acc;
+    }
+}
+
+// State of the pairs between kernels (pst): the input's expansion f, plag =
+// {1/r00, r01, 1/r11}, rho, the scale of the next input, sigma.
+struct PairState {
+    double* hu;     // cu, then (second sweep's) c2a: m + 2 each
+    double* hz;
+    double* h2a;
+    double* h2b;
+    double* f;
+    double* gs;     // 3 + 3 Gram entries
+    double* sc;     // plag[3], rho, input scale, r00
+};
+
+// Columns 2p and 2p + 1 of Hbar, their rotations and the stopping test, and
+// what the next pair needs (one workgroup; formulas above).  nv = 2p + 1.
+__global__ __launch_bounds__(kGT) void k_pair_step(int p, int m, PairState ps, const double* __restrict__ sigp,
+                                                   double* __restrict__ H, double* __restrict__ cs,
+                                                   double* __restrict__ sn, double* __restrict__ g,
+                                                   double* __restrict__ vscale, double vs_new,
+                                                   double* __restrict__ hist, int64_t hist_cap,
+                                                   double* __restrict__ Hraw, Ctrl* ctrl, int gate) {
+    __shared__ double fl[kMaxM + 3], gv[kMaxM + 3], za[kMaxM + 3], b2[kMaxM + 3];
+    __shared__ double c0[kMaxM + 4], c1[kMaxM + 4], cl[kMaxM + 2], sl[kMaxM + 2];
+    __shared__ double rowp[kGT], sc[8];
+    const int tid = threadIdx.x;
+    const int nv = 2 * p + 1, j0 = 2 * p;
+    double cu = 0, cz = 0, a2 = 0, bb2 = 0, fv = 0;
+    if (tid < nv) {
+        cu = ps.hu[tid];
+        cz = ps.hz[tid];
+        a2 = ps.h2a[tid];
+        bb2 = ps.h2b[tid];
+        fv = p > 0 ? ps.f[tid] : 1.0;
+    }
+    if (tid < j0) {
+        cl[tid] = cs[tid];
+        sl[tid] = sn[tid];
+    }
+    const double aa = ps.gs[3], ab = ps.gs[4], bb = ps.gs[5], rho = ps.sc[3], sig = *sigp;
+    if (gated(ctrl, gate)) return;
+    __shared__ double red[kGT / kWave];
+    if (tid < nv) {
+        fl[tid] = fv;
+        gv[tid] = cu + a2;
+        za[tid] = (cz + rho * a2 + bb2) / sig;
+        b2[tid] = bb2;
+    }
+    const double qa = block_sum_n<kGT>(a2 * a2, red);
+    const double qab = block_sum_n<kGT>(a2 * bb2, red);
+    const double qb = block_sum_n<kGT>(bb2 * bb2, red);
+    const double r00 = sqrt(fmax(aa - qa, 0.0));
+    const double i00 = r00 > 0.0 ? 1.0 / r00 : 0.0;
+    const double r01 = (ab - qab) * i00;
+    const double r11 = sqrt(fmax(bb - qb - r01 * r01, 0.0));
+    const double i11 = r11 > 0.0 ? 1.0 / r11 : 0.0;
+    // Row l of Hbar times f (columns < j0) and times g (columns < j0; column
+    // j0 is added below), split over G threads.
+    const int G = max(1, kGT / nv), l = tid % nv, grp = tid / nv;
+    double hf = 0, hg = 0;
+    if (grp < G) {
+        const int k0 = l > 0 ? l - 1 : 0, k1 = j0;
+        const int span = (k1 - k0 + G - 1) / G;
+        const int b0 = k0 + grp * span, b1 = min(k1, b0 + span);
+        for (int k = b0; k < b1; ++k) {
+            const double hv = Hraw[(int64_t)l * m + k];
+            hf += hv * fl[k];
+            hg += hv * gv[k];
+        }
+    }
+    rowp[tid] = hf;
+    __syncthreads();
+    if (tid < nv) {
+        for (int q = 1; q < G; ++q) hf += rowp[q * nv + tid];
+        c0[tid] = (gv[tid] - hf) / fl[j0];
+    }
+    __syncthreads();
+    rowp[tid] = hg;
+    if (tid == 0) c0[nv] = r00 / fl[j0];
+    __syncthreads();
+    if (tid < nv) {
+        for (int q = 1; q < G; ++q) hg += rowp[q * nv + tid];
+        c1[tid] = (za[tid] - hg - c0[tid] * gv[j0]) * i00;
+    }
+    if (tid == 0) {
+        c1[nv] = ((rho * r00 + r01) / sig - c0[nv] * gv[j0]) * i00;
+        c1[nv + 1] = r11 / sig * i00;
+    }
+    __syncthreads();
+    const bool two = j0 + 1 < m;
+    for (int i = tid; i <= nv; i += kGT) Hraw[(int64_t)i * m + j0] = c0[i];
+    if (two)
+        for (int i = tid; i <= nv + 1; i += kGT)
+            if (i <= m) Hraw[(int64_t)i * m + j0 + 1] = c1[i];
+    const double n0 = block_sum_n<kGT>(tid <= nv ? c0[tid] * c0[tid] : 0.0, red);
+    const double n1 = block_sum_n<kGT>(tid <= nv + 1 ? c1[tid] * c1[tid] : 0.0, red);
+    // Next pair: input b / r11 = V f, lagged coefficients, scales.
+    if (tid < nv) ps.f[tid] = b2[tid] * i11;
+    if (tid == 0) {
+        ps.f[nv] = r01 * i11;
+        ps.f[nv + 1] = r11 * i11;
+        ps.sc[0] = i00;
+        ps.sc[1] = r01;
+        ps.sc[2] = i11;
+        ps.sc[4] = i11;
+        ps.sc[5] = i00;
+        if (nv <= m) vscale[nv] = vs_new;
+        if (nv + 1 <= m) vscale[nv + 1] = vs_new;
+    }
+    if (tid != 0) return;
+    // Rotations of the two columns (one lane).
+    int64_t its = ctrl->its;
+    const int64_t maxit = ctrl->max_iters;
+    const double target = ctrl->target;
+    double gj = g[j0];
+    for (int t = 0; t < 2; ++t) {
+        const int j = j0 + t;
+        if (j >= m) break;
+        const double* col = t ? c1 : c0;
+        const double hn = col[j + 1];
+        // The norms come from differences of squares (about sqrt(eps) of
+        // rounding): breakdown below that level of ||P A v_j||.
+        const int bd = !(hn > 1.4901161193847656e-08 * sqrt(t ? n1 : n0));
+        double av = col[0];
+        for (int i = 0; i < j; ++i) {
+            const double c = cl[i], sv = sl[i], b = col[i + 1];
+            H[(int64_t)i * m + j] = c * av + sv * b;
+            av = -sv * av + c * b;
+        }
+        double r = hypot(av, hn), cj = av / r, sj = hn / r;
+        if (hn == 0.0) {
+            cj = 1.0;
+            sj = 0.0;
+            r = av;
+        }
+        cl[j] = cj;
+        sl[j] = sj;
+        cs[j] = cj;
+        sn[j] = sj;
+        H[(int64_t)j * m + j] = r;
+        H[(int64_t)(j + 1) * m + j] = 0.0;
+        g[j] = cj * gj;
+        gj = -sj * gj;
+        g[j + 1] = gj;
+        ++its;
+        if (hist && ctrl->hist_base + its - 1 < hist_cap) hist[ctrl->hist_base + its - 1] = fabs(gj);
+        ctrl->its = its;
+        ctrl->k = j + 1;
+        ctrl->breakdown = bd;
+        const bool est = fabs(gj) <= target;
+        if (est) ctrl->est_conv = 1;
+        if (est || bd || its >= maxit) {
+            ctrl->stop = 1;
+            break;
+        }
+    }
+}
+
+// Back substitution of a cycle of pairs: with k even the last vector is not
+// stored; v_{k-1} = (a - V c2a) / r00 turns its coefficient into one of a and
+// corrections of the others.  coef[i], i < k - (k even): stored columns;
+// coef[kMaxM]: a.
+__global__ __launch_bounds__(kWG) void k_pair_backsolve(int m, const double* __restrict__ H,
+                                                        const double* __restrict__ g,
+                                                        const double* __restrict__ vscale, PairState ps,
+                                                        double* __restrict__ coef, double* __restrict__ coefa,
+                                                        int* cyc_k, int cyc_cap, Ctrl* ctrl, int gate) {
+    if (gated(ctrl, gate)) return;
+    __shared__ double Rl[kMaxM * kMaxM];
+    __shared__ double gl[kMaxM], yl[kMaxM];
+    const int k = ctrl->k;
+    if (threadIdx.x == 0 && cyc_k && ctrl->cycles - 1 < cyc_cap) cyc_k[ctrl->cycles - 1] = k;
+    for (int q = threadIdx.x; q < k * k; q += kWG) {
+        const int i = q / k, c = q % k;
+        Rl[q] = (c >= i) ? H[(int64_t)i * m + c] : 0.0;
+    }
+    for (int i = threadIdx.x; i < k; i += kWG) gl[i] = g[i];
+    __syncthreads();
+    for (int i = k - 1; i >= 0; --i) {
+        const double yi = gl[i] / Rl[i * k + i];
+        for (int l = threadIdx.x; l < i; l += kWG) gl[l] -= Rl[l * k + i] * yi;
+        if (threadIdx.x == 0) yl[i] = yi;
+        __syncthreads();
+    }
+    const bool even = (k & 1) == 0;
+    const double e = even ? yl[k - 1] * ps.sc[5] : 0.0;
+    const int ks = even ? k - 1 : k;
+    for (int i = threadIdx.x; i < ks; i += kWG) coef[i] = (yl[i] - (even ? ps.h2a[i] * e : 0.0)) * vscale[i];
+    if (threadIdx.x == 0) *coefa = e;
+}
+
+// x_hat += V coef + a coefa over the stored columns of the cycle.
+template <typename VT, typename WT>
+__global__ __launch_bounds__(kWG) void k_pair_xupdate(int n, int64_t ldv, const VT* __restrict__ V,
+                                                      const WT* __restrict__ a,
+                                                      const double* __restrict__ coef,
+                                                      const double* __restrict__ coefa,
+                                                      double* __restrict__ xh, Ctrl* ctrl, int gate) {
+    if (gated(ctrl, gate)) return;
+    __shared__ double c_l[kMaxM];
+    const int k = ctrl->k - ((ctrl->k & 1) == 0 ? 1 : 0);
+    for (int t = threadIdx.x; t < k; t += kWG) c_l[t] = coef[t];
+    const double e = *coefa;
+    __syncthreads();
+    const int64_t stride = (int64_t)gridDim.x * kWG;
+    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n; i += stride) {
+        double acc = e != 0.0 ? e * (double)a[i] : 0.0;
+        int t = 0;
+        for (; t + 4 <= k; t += 4) {
+            const double a0 = (double)ld_f(V + t * ldv + i);
+            const double a1 = (double)ld_f(V + (t + 1) * ldv + i);
+            const double a2 = (double)ld_f(V + (t + 2) * ldv + i);
+            const double a3 = (double)ld_f(V + (t + 3) * ldv + i);
+            acc += a0 * c_l[t];
+            acc += a1 * c_l[t + 1];
+            acc += a2 * c_l[t + 2];
+            acc += a3 * c_l[t + 3];
+        }
+        for (; t < k; ++t) acc += (double)ld_f(V + t * ldv + i) * c_l[t];
+        xh[i] += acc;
+    }
+}
+
 // x_hat += sum_{t < k} stored_t * coef[t]  (eq. new_sol); k from the control block.
 template <typename VT>
 __global__ __launch_bounds__(kWG) void k_xupdate(int n, int64_t ldv, const VT* __restrict__ V,
@@ -1756,6 +2319,33 @@ __global__ void k_ctrl_reset(Ctrl* ctrl, int64_t max_iters, int64_t hist_base) {
         c.hist_base = hist_base;
         c.stop = 1;
         *ctrl = c;
+    }
+}
+
+// *out = the power of two just above 1 / max|v| (1 when all are zero or one
+// is not finite), from the per-workgroup maxima of k_absmax.
+__global__ __launch_bounds__(kWG) void k_absmax(const double* __restrict__ v, int64_t n,
+                                                double* __restrict__ part) {
+    __shared__ double red[kWG / kWave];
+    double t = 0;
+    const int64_t stride = (int64_t)gridDim.x * kWG;
+    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n; i += stride) t = fmax(t, fabs(v[i]));
+    for (int o = kWave / 2; o > 0; o >>= 1) t = fmax(t, __shfl_xor(t, o, kWave));
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kWG / kWave; ++q) t = fmax(t, red[q]);
+        part[blockIdx.x] = t;
+    }
+}
+__global__ void k_absmax_scale(const double* __restrict__ part, int nb, double* __restrict__ out) {
+    double t = 0;
+    for (int i = threadIdx.x; i < nb; i += kWave) t = fmax(t, part[i]);
+    for (int o = kWave / 2; o > 0; o >>= 1) t = fmax(t, __shfl_xor(t, o, kWave));
+    if (threadIdx.x == 0) {
+        int ex = 0;
+        if (t > 0.0 && isfinite(t)) frexp(t, &ex);
+        *out = ldexp(1.0, min(max(1 - ex, -1000), 1000));
     }
 }
 
@@ -2233,25 +2823,114 @@ struct Engine {
                e.ctrl, 2);
     }
 
-    // y = scale * A x for the step's input vector x (type XT), with the fused
-    // Z^T y partials when available.
+    // out = scale * A x for the step's input vector x (type XT), with the
+    // fused Z^T out partials when available.
     template <typename XT>
-    void spmv_any(const XT* x, const double* scale) const {
+    void spmv_into(const XT* x, const double* scale, WT* out) const {
         if (e.L == kSell)
-            sell_launch<0, AT, XT, double, WT, ACC>(e, x, scale, nullptr, y(), 0, 2);
+            sell_launch<0, AT, XT, double, WT, ACC>(e, x, scale, nullptr, out, 0, 2);
         else if (fused())
-            stream_fused<0, AT, XT, double, WT, ACC>(e, vals(), x, scale, nullptr, y(), 0, 2);
+            stream_fused<0, AT, XT, double, WT, ACC>(e, vals(), x, scale, nullptr, out, 0, 2);
         else
             spmv_dispatch<AT, XT, WT, ACC>(e.L, e.NB, e.st, e.n, e.rowptr, e.colind, vals(), x, scale,
-                                           y(), e.ctrl, 2);
+                                           out, e.ctrl, 2);
+    }
+    template <typename XT>
+    void spmv_any(const XT* x, const double* scale) const {
+        spmv_into<XT>(x, scale, y());
+    }
+
+    PairState pair_state() const {
+        PairState s;
+        double* q = e.pst;
+        for (double** d : {&s.hu, &s.hz, &s.h2a, &s.h2b, &s.f}) {
+            *d = q;
+            q += e.m + 4;
+        }
+        s.gs = q;
+        s.sc = q + 6;
+        return s;
+    }
+
+    // Pair p of Arnoldi steps (see k_pair1): a in w, b in p, u in r, z in y.
+    void pair(int p) const {
+        const int j0 = 2 * p, nv = j0 + 1, nr = nv - 2;
+        const PairState s = pair_state();
+        WT* u = r();
+        if (e.timer) e.timer->begin(0, j0);
+        if (p == 0) spmv_into<VT>(Vcol(0), e.vscale, e.R > 0 ? y() : u);
+        else spmv_into<WT>(this->p(), s.sc + 4, e.R > 0 ? y() : u);
+        if (e.timer) e.timer->end(0, j0);
+        if (e.R > 0) {
+            if (fused()) coarse_slots(e.s_step, 2);
+            else coarse(y(), e.s_step, 2);
+            k_pdeflate<WT, AT, ACC><<<e.NB, kWG, 0, e.st>>>(e.n, y(), e.azrp, e.azci, azv(), e.azc1, azv1(),
+                                                           e.s_step, e.R, u, e.ctrl, 2);
+        }
+        if (e.timer) e.timer->begin(0, j0);
+        spmv_into<WT>(u, e.sigma_a, y());
+        if (e.timer) e.timer->end(0, j0);
+        if (fused()) coarse_slots(e.s_step, 2);
+        else coarse(y(), e.s_step, 2);
+        int g1 = 0, g2 = 0;
+        if (e.timer) e.timer->begin(1, j0);
+        const double ss = kHalf ? e.nscale : 1.0;
+        if (p == 0) {
+            auto kf = k_pair1<8, 1, true, VT, WT, AT, ACC>;
+            g1 = grid_for((const void*)kf);
+            launch(kf, g1, kWG, 0, e.st, e.n, e.ldv, V(), 1, w(), this->p(), u, y(), e.azrp, e.azci, azv(), e.azc1,
+                   azv1(), e.s_step, e.R, e.coef1, e.coef2, s.sc, ss, e.part, g1, e.ctrl, 2, e.cache_cols);
+        } else {
+            GM_JMAX_SWITCH(nr, VT, ({
+                auto kf = k_pair1<J, LanesForPair<J>::value, false, VT, WT, AT, ACC>;
+                g1 = grid_for((const void*)kf);
+                launch(kf, g1, kWG, 0, e.st, e.n, e.ldv, V(), nr, w(), this->p(), u, y(), e.azrp, e.azci, azv(),
+                       e.azc1, azv1(), e.s_step, e.R, e.coef1, e.coef2, s.sc, ss, e.part, g1, e.ctrl, 2,
+                       e.cache_cols);
+            }));
+        }
+        if (e.timer) e.timer->end(1, j0);
+        k_pair_finish<<<2 * nv + 3, kWG, 0, e.st>>>(e.part, g1, nv, e.vscale, s.hu, s.hz, e.coef1, e.coef2,
+                                                    s.gs, e.ctrl, 2);
+        if (e.timer) e.timer->begin(2, j0);
+        GM_JMAX_SWITCH(nv, VT, ({
+            auto kf = k_pair2<J, LanesForPair<J>::value, VT, WT, ACC>;
+            g2 = grid_for((const void*)kf);
+            launch(kf, g2, kWG, 0, e.st, e.n, e.ldv, V(), nv, u, y(), w(), this->p(), e.coef1, e.coef2, s.hu, s.hz,
+                   s.gs, s.sc + 3, e.part, g2, e.ctrl, 2, e.cache_cols);
+        }));
+        if (e.timer) e.timer->end(2, j0);
+        k_pair_finish<<<2 * nv + 3, kWG, 0, e.st>>>(e.part, g2, nv, e.vscale, s.h2a, s.h2b, e.coef1, e.coef2,
+                                                    s.gs + 3, e.ctrl, 2);
+        k_pair_step<<<1, kGT, 0, e.st>>>(p, e.m, s, e.sigma_a, e.H, e.cs, e.sn, e.g, e.vscale,
+                                         kHalf ? 1.0 / e.nscale : 1.0, e.hist, e.hist_cap, e.Hraw, e.ctrl, 2);
+    }
+
+    template <typename BT>
+    void pair_cycle(const BT* b) const {
+        for (int p = 0; 2 * p < e.m; ++p) pair(p);
+        const PairState s = pair_state();
+        k_pair_backsolve<<<1, kWG, 0, e.st>>>(e.m, e.H, e.g, e.vscale, s, e.coef1, s.sc + 6, e.cyc_k, e.cyc_cap,
+                                              e.ctrl, 1);
+        k_pair_xupdate<VT, WT><<<e.NB, kWG, 0, e.st>>>(e.n, e.ldv, V(), w(), e.coef1, s.sc + 6, e.xh, e.ctrl, 1);
+        restart_block(b, false, 0.0, 0.0);
     }
 
     template <typename BT>
     void cycle(const BT* b) const {
+        if (e.paired) {
+            pair_cycle(b);
+            return;
+        }
         for (int j = 0; j < e.m; ++j) {
-            if (e.dcgs) step_dc(j);
-            else if (e.lagged) step_lag(j);
-            else step(j);
+            if (e.dcgs) {
+                step_dc(j);
+            } else if (e.lagged) {
+                // Adaptive deflation only (FP64).
+                if constexpr (std::is_same<VT, double>::value) step_lag(j);
+            } else {
+                step(j);
+            }
         }
         if constexpr (std::is_same<VT, double>::value && std::is_same<WT, double>::value)
             if (e.dcgs) dc_dots<false>(e.m);
@@ -2386,6 +3065,12 @@ void launch_axpy_norm(hipStream_t st, int NB, int n, const double* nrm2, const d
 
 void launch_ctrl_reset(hipStream_t st, Ctrl* c, int64_t max_iters, int64_t hist_base) {
     k_ctrl_reset<<<1, 64, 0, st>>>(c, max_iters, hist_base);
+}
+
+void launch_value_scale(hipStream_t st, const double* v, int64_t n, double* part, int cap, double* out) {
+    const int nb = (int)std::max<int64_t>(1, std::min<int64_t>((n + kWG - 1) / kWG, std::min(cap, 1024)));
+    k_absmax<<<nb, kWG, 0, st>>>(v, n, part);
+    k_absmax_scale<<<1, kWave, 0, st>>>(part, nb, out);
 }
 
 void launch_fill(hipStream_t st, double* p, int64_t n, double v) {
