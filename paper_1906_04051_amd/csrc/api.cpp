@@ -322,7 +322,7 @@ void carve_gang(gmres_plan_s* p, Arena& A) {
     for (int s = 0; s < p->nsys; ++s) rmax = std::max(rmax, p->zcol_off[s + 1] - p->zcol_off[s]);
     p->gang_flags = A.take_n<unsigned>(kGangWG * kGangFlagWords);
     p->gang_args = A.take_n<char>((int64_t)gang_args_bytes());
-    p->gang_part = A.take_n<double>(3 * (int64_t)gang_ps(p->o.m + 2) * kGangWG);
+    p->gang_part = A.take_n<double>(3 * (int64_t)gang_ps(p->o.m + 2 + (p->o.adapt_rmax > 0 ? 24 : 0)) * kGangWG);
     if (rmax > 0) {
         p->gang_bmap = A.take_n<unsigned>(8 * kGangWG);
         p->gang_tpart = A.take_n<double>(2 * (int64_t)gang_ps((int)rmax) * kGangWG);
@@ -1022,9 +1022,8 @@ gmres_status run_engine(gmres_plan_s* p, int op, int prec, const void* b, double
 
 // Launch shape of a gang solve (gang.hip) for one engine, or K = 0 where the
 // kernel-per-phase engine runs: an explicit SpMV, grid or orthogonalisation
-// choice, kernel timing, no sliced-ELL copy, adaptive deflation, or a size
-// past the lines below.  256 rows a workgroup (a wavefront per SIMD) until
-// every compute unit has one.  Measured, us per step, gang / engine:
+// choice, kernel timing, no sliced-ELL copy, or a size past the lines below.
+// 256 rows a workgroup (a wavefront per SIMD) until every compute unit has one.  Measured, us per step, gang / engine:
 //   FP64, 64 indicators: 66,049 rows, m = 50: 19.5 / 46; 263,169, m = 30:
 //   38 / 62; 361,201, m = 50 (589 KB of basis a workgroup): 58 / 72, m = 80
 //   (942 KB): 91 / 88; 491,401 (four rows a thread, spills), m = 30: 69 / 72,
@@ -1040,7 +1039,7 @@ struct GangShape {
 GangShape gang_shape(const gmres_plan_s* p, int op, int prec) {
     GangShape g;
     const bool sell = op ? p->tsell_col != nullptr : p->sell_col != nullptr;
-    if (p->nsys != 1 || p->o.ortho != 1 || p->adapt.rmax > 0 || p->timer.period > 0 || !sell ||
+    if (p->nsys != 1 || p->o.ortho != 1 || p->timer.period > 0 || !sell ||
         (p->o.spmv_lanes != 0 && p->o.spmv_lanes != kSell) || p->o.num_blocks > 0)
         return g;
     int cus = 0, lds_max = 0;
@@ -1104,6 +1103,16 @@ void gang_args(gmres_plan_s* p, int op, int prec, GangHot& h, GangArgs& a) {
     a.hist_base = p->hist_pos;
     a.cyc_k = e.cyc_k;
     a.cyc_cap = e.cyc_cap;
+    if (e.adapt) {
+        a.ast = e.adapt->st;
+        a.aU = e.adapt->U;
+        a.aAU = e.adapt->AU;
+        a.aC = e.adapt->C;
+        a.ald = e.adapt->rmax + 1;
+        a.Hraw = e.Hraw;
+        a.coef = e.coef1;
+        a.vscale = e.vscale;
+    }
 }
 
 // Runs a whole solve of one engine from p->xh in gang launches; b: right-hand
@@ -1129,7 +1138,8 @@ gmres_status run_gang(gmres_plan_s* p, int op, int prec, const void* b, double r
     a.b = b;
     a.xout = xout;
     // A launch ends after about this many steps and the next one resumes.
-    a.max_cycles = std::max(1, 8192 / p->o.m);
+    // (adaptive deflation: one cycle, then its Ritz step on its own kernels).
+    a.max_cycles = a.ast ? 1 : std::max(1, 8192 / p->o.m);
     // The basis buffer may hold this precision's columns: an engine of another
     // one clears it first.
     if (p->last_prec != prec) p->last_prec = -1;
@@ -1140,6 +1150,7 @@ gmres_status run_gang(gmres_plan_s* p, int op, int prec, const void* b, double r
         *out = p->ctrl_h[0];
         if (out->pad32 != 0) return GMRES_OK;
         if (out->done) break;
+        if (a.ast) adapt_cycle_end(make_args(p, op, prec), static_cast<const double*>(p->V), p->coef1);
         a.resume = 1;
     }
     p->hist_pos += out->its;
@@ -1220,6 +1231,7 @@ gmres_status solve_f64(gmres_plan_s* p, int op, const double* b, const double* x
     start_x();
     Ctrl c{};
     bool ran = false;
+    if (op == 0 && p->adapt.rmax > 0) adapt_reset(p->st, p->adapt);   // U starts empty
     // With a start vector (which x may be) the result passes through r64, so a
     // repeat on the per-phase engine still finds x0.
     double* xo = x0 ? p->r64 : x;

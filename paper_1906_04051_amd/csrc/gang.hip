@@ -25,6 +25,16 @@
 // cache is written back or invalidated and the matrix stays in L2.  A poll
 // gives up after kSpinTicks: the launch then ends with the abort word set and
 // the host repeats the solve on the kernel-per-phase engine.
+//
+// Adaptive deflation (MODE == kGangAdapt; adapt.hip): M^{-1} changes at every
+// restart and its update needs the basis, so a launch runs one cycle.  Within
+// it U^T x rides on the exchange that already carries the second projection's
+// sums (no further rendezvous) and A U C U^T x is added behind the SpMV; the
+// basis goes to memory once, at the end, for the Ritz step's kernels.  Bratu
+// 20^3 (Newton, 350 steps of m = 50): 21 us a step, 50 on the per-phase engine;
+// a whole Newton solve 21.2 -> 12.3 ms.  66,049 rows, m = 50, 8 cycles of up to
+// 22 columns: 32 us a step, Ritz steps included, 67 on the per-phase engine;
+// 361,201 rows, m = 30: 63 / 101.
 #include "internal.hpp"
 
 namespace gm {
@@ -271,23 +281,26 @@ __device__ __forceinline__ void gang_rows(int nc, const double* part, int ps, in
 // The small state has a fixed place in LDS (immediate addresses); the
 // Hessenberg (packed columns), the cached rows of E^{-1} and the basis follow
 // in the dynamic part.
+constexpr int kGangSingle = 0, kGangBatch = 1, kGangAdapt = 2;
 constexpr int kMP = (kMaxM + 9) & ~7;   // slots per column array
+constexpr int kAU = 24;                 // adaptive deflation columns (kAdaptMax rounded up)
 constexpr int kZS = 64;                 // Z columns summed per round
 __host__ __device__ inline int gang_hraw(int m) { return ((m * (m + 3) / 2) + 7) & ~7; }
 
-template <typename AT, typename VT, typename WT, typename BT, typename ACC, int RPT, int WF, bool BATCH>
+template <typename AT, typename VT, typename WT, typename BT, typename ACC, int RPT, int WF, int MODE>
 __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
     // Arguments of the cold paths are read from memory where they are used
     // (they would otherwise fill the scalar registers of the step loop).
     const GangArgs& a = *ac;
+    constexpr bool BATCH = MODE == kGangBatch, ADAPT = MODE == kGangAdapt;
     extern __shared__ double dyn[];
-    __shared__ double cs[kMP], sn[kMP], gl[kMP], h1[kMP], h2[kMP], ds[kMP];
+    __shared__ double cs[kMP], sn[kMP], gl[kMP], h1[kMP], h2[kMP], ds[kMP + kAU];
     __shared__ ACC c1[kMP], c2[kMP];           // coefficients of the sweeps
-    __shared__ double red[kGW][kMP + 8];       // per-wave dots
+    __shared__ double red[kGW][kMP + 8 + kAU]; // per-wave dots, norm at kMP, U dots from kMP + 8
     __shared__ double grow[kGW][2 * kWave];    // per-wave sums over the members
     __shared__ double zred[kGW][kZS];          // per-wave Z^T sums
     __shared__ double tv[kMaxR], sv[kMaxR];    // t = Z^T u, s = E^{-1} t
-    __shared__ double sc[4];                   // hn, 1 / hn
+    __shared__ double su[ADAPT ? kAU : 1];     // C U^T x
     __shared__ int zl[kMaxR], al[kMaxR];       // own Z columns; columns whose s is needed
     __shared__ int rng[kMaxR];                 // members [lo, hi) touching each column
     __shared__ unsigned bits[32];              // 8 words Z, 8 words A Z
@@ -307,7 +320,7 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
     const int first = (int)blockIdx.x - me;
     unsigned epoch = 0;
     unsigned* flags = h.flags + first * kFlagW;
-    const int ps = gang_ps(m + 2), ts = gang_ps(h.Rmax);   // row strides
+    const int ps = gang_ps(m + 2 + (ADAPT ? kAU : 0)), ts = gang_ps(h.Rmax);   // row strides
     // Exchange e of the gang uses slot e % 3: a workgroup empties its row of
     // exchange e once it has collected e + 1 (which everyone published after
     // collecting e), and waits for that store before it publishes e + 2, so a
@@ -375,11 +388,11 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
         // zero: rows past the end hold 0, slots past the last column repeat
         // it with coefficient 0.
         for (int i = tid; i < min(nl, m) * RW; i += kGN) Vl[i] = (ST)0;
-        for (int i = tid; i < kGW * (kMP + 8); i += kGN) red[0][i] = 0.0;
-        // Position in global overflow columns (every row slot has a valid one).
+        for (int i = tid; i < kGW * (kMP + 8 + kAU); i += kGN) red[0][i] = 0.0;
+        // Place in global overflow columns (every row slot has a valid one).
         int64_t gpos[RPT];
 #pragma unroll
-        for (int q = 0; q < RPT; ++q) gpos[q] = ok[q] ? p0 + pos[q] : min(p0, n - 1);
+        for (int q = 0; q < RPT; ++q) gpos[q] = ok[q] ? row[q] : 0;
 
         // Rows without A Z entries multiply s_0 by zero, listed or not.
         for (int i = tid; i < kMaxR; i += kGN) sv[i] = 0.0;
@@ -789,9 +802,36 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
             }
             return ok[q] ? (ACC)t : (ACC)0;
         };
+        // Adaptive deflation: columns of U in use; y += (A U) C U^T x.
+        const int ru = ADAPT ? uni(a.ast->r) : 0;
+        // su = C tu with tu = ds[at ..] (a barrier follows in the caller).
+        auto ucoarse = [&](int at) {
+            for (int i = tid >> 3; i < ru; i += kGN / 8) {
+                double t = 0;
+                for (int q = tid & 7; q < ru; q += 8) t += a.aC[i * a.ald + q] * ds[at + q];
+                t = ggroup_sum(t, 8);
+                if ((tid & 7) == 0) su[i] = t;
+            }
+            __syncthreads();
+        };
+        auto ucorrect = [&](ACC (&u)[RPT]) {
+#pragma unroll
+            for (int q = 0; q < RPT; ++q) {
+                if (!ok[q]) continue;
+                const double* p = a.aAU + row[q];
+                for (int c = 0; c < ru; c += 8) {
+                    double v[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] = p[min(c + e, ru - 1) * h.ldv];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) u[q] += c + e < ru ? (ACC)(v[e] * su[c + e]) : (ACC)0;
+                }
+            }
+        };
         // Publishes the own rows' partial dots of u with columns 0 .. nv-1 and
-        // ||u||^2 (entry nv); with K = 1 they go to ds.
-        auto dots = [&](int nv, const ACC (&u)[RPT]) {
+        // ||u||^2 (entry nv) and, with the adaptive deflation (ud), with the
+        // columns of U (entries from nv + 1); with K = 1 they go to ds.
+        auto dots = [&](int nv, const ACC (&u)[RPT], bool ud = false) {
             if (wact) {
                 int c = 0;
                 for (; c + 8 < nv; c += 16) {
@@ -827,6 +867,20 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                     const ACC z = gsum8(acc, ln);
                     if ((ln & 7) == 0) red[wv][c + gsum8_col(ln)] = (double)z;
                 }
+                if (ADAPT && ud)
+                    for (int k = 0; k < ru; k += 8) {
+                        ACC acc[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) acc[e] = 0;
+#pragma unroll
+                        for (int q = 0; q < RPT; ++q) {
+                            const double* p = a.aU + row[q];
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) acc[e] += (ACC)p[min(k + e, ru - 1) * h.ldv] * u[q];
+                        }
+                        const ACC z = gsum8(acc, ln);
+                        if ((ln & 7) == 0) red[wv][kMP + 8 + k + gsum8_col(ln)] = (double)z;
+                    }
                 ACC t = 0;
 #pragma unroll
                 for (int q = 0; q < RPT; ++q) t += u[q] * u[q];
@@ -837,8 +891,8 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
             // before the row is published.
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            if (tid <= nv) {
-                const int c = tid < nv ? tid : kMP;
+            if (tid <= nv + (ADAPT && ud ? ru : 0)) {
+                const int c = tid < nv ? tid : (tid == nv ? kMP : kMP + 8 + (tid - nv - 1));
                 double t = red[0][c];
 #pragma unroll
                 for (int q = 1; q < kGW; ++q) t += red[q][c];
@@ -957,19 +1011,21 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
             for (int q = 0; q < RPT; ++q) {
                 const ACC v = vput(0, q, u[q] * st0);
                 if (ok[q]) st_ag(w + row[q], (WT)(v * (ACC)vs));
-                u[q] = 0;
+                u[q] = ADAPT ? v : (ACC)0;
             }
             if (tid == 0) gl[0] = beta;
             ACC wr[RPT];      // this thread's entries of the current vector
-            dots(0, u);       // v_0 is in memory (the sum itself is not used)
+            dots(0, u, ADAPT);   // v_0 is in memory (the norm itself is not used)
             int j = 0;
             double wpre2 = 0.0;
             for (;; ++j) {
                 // Step j: SpMV on w; meanwhile column j - 1 is finished.
                 const bool last = j == m || (j > 0 && left <= 1);
-                COLLECT(j > 0 ? j + 1 : 1);
+                COLLECT((j > 0 ? j + 1 : 1) + (ADAPT ? ru : 0));
                 if (!last) {
+                    if (ADAPT && ru > 0) ucoarse(j > 0 ? j + 1 : 1);
                     spmv(w, u);
+                    if (ADAPT && ru > 0) ucorrect(u);
 #pragma unroll
                     for (int q = 0; q < RPT; ++q) u[q] = (ACC)(WT)u[q];
                     if (R > 0) {
@@ -1122,11 +1178,19 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                         if (ok[q]) st_ag(w + row[q], (WT)wr[q]);
                     }
                 }
-                dots(j + 1, wr);
+                dots(j + 1, wr, ADAPT);
             }
             // After the last column: its estimate.
             __syncthreads();
             if (uni(si[3])) est_conv = 1;
+            if (ADAPT && me == 0) {
+                // The Ritz step outside reads the unrotated matrix.
+                for (int i = tid; i < kk * (kk + 1); i += kGN) {
+                    const int r = i / kk, q = i - r * kk;
+                    if (r <= q + 1) a.Hraw[(int64_t)r * m + q] = Hr[q * (q + 3) / 2 + r];
+                }
+                __syncthreads();
+            }
             // R from the unrotated columns (thread per column, in place), then
             // the back substitution by one wavefront (g and y in registers).
             __syncthreads();
@@ -1154,6 +1218,21 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                 }
             }
             __syncthreads();
+            if constexpr (ADAPT) {
+                // x += M^{-1} V y and the new Ritz vector are formed outside:
+                // the basis goes to memory, its coefficients beside it.
+#pragma unroll
+                for (int q = 0; q < RPT; ++q)
+                    if (ok[q])
+                        for (int k = 0; k < min(kk, nl); ++k)
+                            ((GM_GLB ST*)Vg)[k * ldv + gpos[q]] = Vl[k * RW + pos[q]];
+                if (me == 0) {
+                    if (tid < kk) a.coef[tid] = ds[tid];
+                    if (tid <= kk) a.vscale[tid] = 1.0;
+                    if (tid == 0 && a.cyc_k && cycles - 1 < a.cyc_cap) a.cyc_k[cycles - 1] = kk;
+                }
+                break;
+            }
 #pragma unroll
             for (int q = 0; q < RPT; ++q) {
                 if (!ok[q]) continue;
@@ -1224,22 +1303,23 @@ __global__ void k_gang_clear(GangArgs a, GangArgs* dst, unsigned* flags, int nwg
 }
 
 // ------------------------------------------------------------------------ host
-template <typename AT, typename VT, typename WT, typename BT, typename ACC, bool BATCH>
+template <typename AT, typename VT, typename WT, typename BT, typename ACC, int MODE>
 static const void* gang_fn(int rpt, bool w9) {
     if (rpt == 1)
-        return w9 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 1, 9, BATCH>
-                  : (const void*)k_gang<AT, VT, WT, BT, ACC, 1, 0, BATCH>;
+        return w9 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 1, 9, MODE>
+                  : (const void*)k_gang<AT, VT, WT, BT, ACC, 1, 0, MODE>;
     if (rpt == 2)
-        return w9 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 2, 9, BATCH>
-                  : (const void*)k_gang<AT, VT, WT, BT, ACC, 2, 0, BATCH>;
+        return w9 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 2, 9, MODE>
+                  : (const void*)k_gang<AT, VT, WT, BT, ACC, 2, 0, MODE>;
     // No registers left for the matrix.
-    return rpt == 3 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 3, 0, BATCH>
-                    : (const void*)k_gang<AT, VT, WT, BT, ACC, 4, 0, BATCH>;
+    return rpt == 3 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 3, 0, MODE>
+                    : (const void*)k_gang<AT, VT, WT, BT, ACC, 4, 0, MODE>;
 }
 
 size_t gang_lds_fixed(int m, int prec) {
     const size_t acc = prec == kPrecF64 ? 8 : 4;
-    return 8 * (6 * (size_t)kMP + kGW * (kMP + 8) + kGW * 2 * kWave + kGW * kZS + 2 * kMaxR + 4) + 2 * acc * kMP +
+    return 8 * (6 * (size_t)kMP + 2 * kAU + kGW * (kMP + 8 + kAU) + kGW * 2 * kWave + kGW * kZS + 2 * kMaxR) +
+           2 * acc * kMP +
            4 * (3 * kMaxR + 32 + 8) + 256 + 8 * (size_t)gang_hraw(m);
 }
 
@@ -1248,10 +1328,11 @@ size_t gang_args_bytes() { return sizeof(GangArgs); }
 bool launch_gang(const GangHot& h0, const GangArgs& a, void* args_d, int prec, int rpt, bool w9, int nwg,
                  int nticket) {
     GangHot h = h0;
-    const void* f = a.row_off          ? gang_fn<double, double, double, double, double, true>(rpt, w9)
-                    : prec == kPrecF64 ? gang_fn<double, double, double, double, double, false>(rpt, w9)
-                    : prec == kPrecF32 ? gang_fn<float, float, float, float, float, false>(rpt, w9)
-                                       : gang_fn<float, __half, float, float, float, false>(rpt, w9);
+    const void* f = a.row_off          ? gang_fn<double, double, double, double, double, kGangBatch>(rpt, w9)
+                    : a.ast            ? gang_fn<double, double, double, double, double, kGangAdapt>(rpt, w9)
+                    : prec == kPrecF64 ? gang_fn<double, double, double, double, double, kGangSingle>(rpt, w9)
+                    : prec == kPrecF32 ? gang_fn<float, float, float, float, float, kGangSingle>(rpt, w9)
+                                       : gang_fn<float, __half, float, float, float, kGangSingle>(rpt, w9);
     const size_t dynb = 8 * (size_t)gang_hraw(h.m) + h.ecap + h.vcap;
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dynb) != hipSuccess) {
         (void)hipGetLastError();

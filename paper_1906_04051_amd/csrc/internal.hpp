@@ -329,6 +329,11 @@ struct GangArgs {
     int64_t hist_cap, hist_base;
     int* cyc_k;
     int cyc_cap;
+    // adaptive deflation (ast = nullptr: none): one cycle a launch
+    const AdaptState* ast;
+    const double *aU, *aAU, *aC;
+    int ald;                  // leading dimension of C
+    double *Hraw, *coef, *vscale;
     // batch
     int ncls;
     const int *wg_member, *wg_size, *wg_class, *cls_ptr, *order;

@@ -88,6 +88,25 @@ def test_gang_mixed_reaches_tolerance(prec, mesh):
     _close(xg, xe, prec)
 
 
+@pytest.mark.parametrize("mesh,m,rmax,steps", [
+    (15, 7, 2, 40),       # one workgroup; columns of U removed
+    (40, 20, 22, 130),    # fewer cycles than columns
+    (128, 64, 9, 150),    # U's columns cross a group of eight
+    (362, 12, 3, 50),     # two row slots
+    (512, 30, 4, 70),     # three row slots, basis beyond LDS
+])
+def test_gang_adaptive_matches_engine(mesh, m, rmax, steps):
+    """One launch a cycle, the Ritz step between them."""
+    sysm = W.convection_diffusion_manufactured(mesh, beta=(20.0, 5.0), s=0)
+    kw = dict(m=m, rtol=0.0, max_iters=steps, adapt_rmax=rmax, record_history=1)
+    xg, ig, hg = _solve(sysm, **kw)
+    xe, ie, he = _solve(sysm, num_blocks=64, **kw)
+    assert ig["iters"] == ie["iters"] == steps and ig["cycles"] == ie["cycles"]
+    assert ig["defl_r"] == ie["defl_r"]
+    _close(xg, xe, "engine")
+    _close(hg, he, "history")
+
+
 def test_gang_solve_longer_than_one_launch():
     """m = 2: a launch ends after 4,096 cycles; the next ones resume."""
     s = W.convection_diffusion_manufactured(20, beta=(60.0, 10.0), s=0)
