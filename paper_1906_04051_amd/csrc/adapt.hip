@@ -200,7 +200,7 @@ __global__ __launch_bounds__(kWG) void k_vcomb(int n, int64_t ldv, const double*
 
 // ----------------------------------------------------- small dense kernels
 // Work on k x k row-major matrices in LDS with one wavefront (kSW threads,
-// rows i = lane, lane + kSW, ...).
+// rows i = lane, lane + kSW, ...): T, of at most r_max + 1 columns.
 
 __device__ __forceinline__ double sw_sum(double v) { return wave_sum(v); }
 
@@ -309,48 +309,242 @@ __device__ void sw_lu_solve(int k, const double* LU, const int* piv, double* z) 
 // Ritz step of one restart: |mu| by power iteration on H_k, the eigenvector
 // of H_k's smallest eigenvalue by inverse iteration; zc = z_i * vscale[i]
 // (coefficients on the stored basis).  st->ok = 0 when H_k is singular.
-__global__ __launch_bounds__(kSW) void k_ritz(int m, const double* __restrict__ Hraw,
-                                              const double* __restrict__ vscale,
-                                              AdaptState* __restrict__ st,
-                                              double* __restrict__ zc, const Ctrl* ctrl, int gate) {
-    __shared__ double H[kMaxM * kMaxM];
-    __shared__ double z[kMaxM], z2[kMaxM];
-    __shared__ int piv[kMaxM];
+//
+// Both iterations are serial chains of small steps, so the kernel is bound by
+// the latency of each; they are independent, so one wavefront runs each, with
+// no workgroup barrier.  Lane i holds entries i and i + 64 of the vector.  H_k
+// is upper Hessenberg: column p has one entry below the diagonal, so a pivot
+// is chosen from two rows, L is a product of k - 1 two-row steps, and the
+// elimination is one row operation a column (the dense sw_lu does k - p).  The
+// pivots and multipliers are those of sw_lu; U's columns are scaled by their
+// pivots' reciprocals, so a back substitution step is a broadcast and one
+// multiply-add.  Operands from LDS are read eight steps ahead of the chain.  k = 50: 509 us with the dense
+// single-wavefront form, 105 us now.
+constexpr int kRL = kMaxM + 1;   // column stride in LDS (odd: rows and columns without conflicts)
+
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {   // lane: uniform
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, lane);
+    const unsigned hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double entry(double v0, double v1, int p) {   // p: uniform
+    return p < kWave ? lane_value(v0, p) : lane_value(v1, p - kWave);
+}
+
+// kKP power iterations on H (column stride kRL) from ones / sqrt(k); ||H z||.
+__device__ double ritz_power(int k, const double* H, double* z) {
+    const int ln = threadIdx.x & (kWave - 1);
+    const bool two = k > kWave;
+    const double* h0 = H + (ln < k ? ln : 0);
+    const double* h1 = H + (ln + kWave < k ? ln + kWave : 0);
+    for (int i = ln; i < k; i += kWave) z[i] = 1.0 / sqrt((double)k);
+    for (int it = 0;; ++it) {
+        wave_lds_sync();
+        double v0 = 0, v1 = 0;
+#pragma unroll 8
+        for (int q = 0; q < k; ++q) v0 += h0[q * kRL] * z[q];
+        if (two)
+#pragma unroll 8
+            for (int q = 0; q < k; ++q) v1 += h1[q * kRL] * z[q];
+        if (ln >= k) v0 = 0;
+        if (ln + kWave >= k) v1 = 0;
+        const double nz = sqrt(gwave_sum(v0 * v0 + v1 * v1));
+        if (it == kKP || nz == 0.0) return nz;
+        wave_lds_sync();
+        if (ln < k) z[ln] = v0 / nz;
+        if (ln + kWave < k) z[ln + kWave] = v1 / nz;
+    }
+}
+
+// H = P L U' D with row exchanges between neighbours: U' (unit upper, column
+// stride kRL, only its strict part kept, zeros elsewhere), the reciprocal
+// pivots inv, multipliers lm and exchange marks ex (bit p); false when
+// |pivot| <= k eps max|H|.  lm holds kRP entries, U kRP a column.
+constexpr int kRP = (kMaxM + 7) & ~7;
+
+__device__ bool ritz_lu(int k, const double* H, double* U, double* inv, double* lm,
+                        unsigned long long (&ex)[2]) {
+    const int ln = threadIdx.x & (kWave - 1);
+    const int q0 = ln < k ? ln : k - 1, q1 = ln + kWave < k ? ln + kWave : k - 1;
+    double mx = 0;
+#pragma unroll 8
+    for (int q = 0; q < k; ++q) mx = fmax(mx, fmax(fabs(H[q * kRL + q0]), fabs(H[q * kRL + q1])));
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, kWave));
+    const double tiny = (double)k * 2.220446049250313e-16 * mx;
+    for (int q = 0; q < k; ++q) {
+        U[q * kRL + ln] = 0.0;
+        if (ln < kRP - kWave) U[q * kRL + kWave + ln] = 0.0;
+    }
+    if (ln < kRP) lm[ln] = 0.0;
+    if (ln + kWave < kRP) lm[ln + kWave] = 0.0;
+    wave_lds_sync();
+    ex[0] = ex[1] = 0;
+    double c0 = H[q0 * kRL], c1 = H[q1 * kRL];   // the row being reduced
+    double m0 = k > 1 ? H[q0 * kRL + 1] : 0.0, m1 = k > 1 ? H[q1 * kRL + 1] : 0.0;
+    double i0 = 0, i1 = 0;
+    for (int p = 0; p < k; ++p) {
+        const bool more = p + 1 < k;
+        const double n0 = m0, n1 = m1;
+        if (p + 2 < k) {
+            m0 = H[q0 * kRL + p + 2];
+            m1 = H[q1 * kRL + p + 2];
+        }
+        const double a = entry(c0, c1, p), b = more ? entry(n0, n1, p) : 0.0;
+        double bv = -1.0;
+        if (fabs(a) > bv) bv = fabs(a);
+        const bool x = more && fabs(b) > bv;
+        if (x) bv = fabs(b);
+        if (!(bv > tiny)) return false;
+        const double d = x ? b : a, l = more ? (x ? a : b) / d : 0.0;
+        const double p0 = x ? n0 : c0, p1 = x ? n1 : c1;
+        const double o0 = x ? c0 : n0, o1 = x ? c1 : n1;
+        // Row p of U; column q is scaled by its own pivot's reciprocal below.
+        if (ln > p && ln < k) U[q0 * kRL + p] = p0;
+        if (ln + kWave > p && ln + kWave < k) U[q1 * kRL + p] = p1;
+        if (ln == p) i0 = 1.0 / d;
+        if (ln + kWave == p) i1 = 1.0 / d;
+        if (ln == 0) lm[p] = l;
+        if (x) ex[p >> 6] |= 1ull << (p & 63);
+        c0 = o0 - l * p0;
+        c1 = o1 - l * p1;
+    }
+    if (ln < k) inv[ln] = i0;
+    if (ln + kWave < k) inv[ln + kWave] = i1;
+    wave_lds_sync();
+#pragma unroll 8
+    for (int q = 0; q < k; ++q) {
+        const double s = inv[q];
+        U[q * kRL + ln] *= s;
+        if (ln < kRP - kWave) U[q * kRL + kWave + ln] *= s;
+    }
+    wave_lds_sync();
+    return true;
+}
+
+// Eight steps of the two-row eliminations: cur is the entry being carried,
+// zs / lm the input and the multipliers from step p0 on; lane p - off of out
+// receives entry p.
+__device__ __forceinline__ void ritz_fwd8(int p0, int off, const double* zs, const double* lm,
+                                          unsigned ex, double& cur, double& out) {
+    const int at = (threadIdx.x & (kWave - 1)) + off - p0;
+    double nx[8], l[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        nx[e] = zs[p0 + 1 + e];
+        l[e] = lm[p0 + e];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const bool x = (ex >> e) & 1;
+        const double a = x ? nx[e] : cur, b = x ? cur : nx[e];
+        out = at == e ? a : out;
+        cur = b - l[e] * a;
+    }
+}
+
+// (z0, z1) <- (P L U' D)^{-1} z; zs: scratch of kRP + 8 entries, those from k
+// on finite.  Entry p is final once the columns behind it are subtracted, so
+// the products with the reciprocals are taken at the end.
+__device__ __forceinline__ void ritz_solve(int k, const double* U, double i0, double i1, const double* lm,
+                                           const unsigned long long (&ex)[2], double* zs, double& z0,
+                                           double& z1) {
+    const int ln = threadIdx.x & (kWave - 1);
+    wave_lds_sync();
+    if (ln < k) zs[ln] = z0;
+    if (ln + kWave < k) zs[ln + kWave] = z1;
+    wave_lds_sync();
+    double cur = zs[0];
+    for (int p = 0; p < k && p < kWave; p += 8) ritz_fwd8(p, 0, zs, lm, (unsigned)(ex[0] >> p), cur, z0);
+    for (int p = kWave; p < k; p += 8) ritz_fwd8(p, kWave, zs, lm, (unsigned)(ex[1] >> (p - kWave)), cur, z1);
+    z0 = ln < k ? z0 : 0.0;
+    z1 = ln + kWave < k ? z1 : 0.0;
+    int p = (k - 1) | 7;      // columns past k - 1 repeat it with weight zero
+    for (; p >= kWave; p -= 8) {
+        double u0[8], u1[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int c = p - e < k ? p - e : k - 1;
+            u0[e] = U[c * kRL + ln];
+            u1[e] = U[c * kRL + (ln < kRP - kWave ? kWave + ln : kWave)];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const double zp = p - e < k ? lane_value(z1, p - e - kWave) : 0.0;
+            z0 -= u0[e] * zp;
+            z1 -= u1[e] * zp;
+        }
+    }
+    for (; p >= 0; p -= 8) {
+        double u0[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u0[e] = U[(p - e < k ? p - e : k - 1) * kRL + ln];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) z0 -= u0[e] * (p - e < k ? lane_value(z0, p - e) : 0.0);
+    }
+    z0 *= i0;
+    z1 *= i1;
+}
+
+__global__ __launch_bounds__(2 * kWave) void k_ritz(int m, const double* __restrict__ Hraw,
+                                                    const double* __restrict__ vscale,
+                                                    AdaptState* __restrict__ st,
+                                                    double* __restrict__ zc, const Ctrl* ctrl, int gate) {
+    __shared__ double H[kMaxM * kRL], U[kMaxM * kRL];   // column-major
+    __shared__ double zp[kMaxM], zs[kRP + 8], inv[kMaxM], lm[kRP];
     if (gated(ctrl, gate)) return;
     const int k = ctrl->k;
-    const int ln = threadIdx.x;
+    const int ln = threadIdx.x & (kWave - 1);
     if (k < 1) {
-        if (ln == 0) st->ok = 0;
+        if (threadIdx.x == 0) st->ok = 0;
         return;
     }
     // Only the Hessenberg band (rows i <= q + 1 of column q) is ever written;
     // the entries below it are zero by definition, not read from memory.
-    for (int e = ln; e < k * k; e += kSW) {
-        const int i = e / k, q = e % k;
-        H[e] = (i <= q + 1) ? Hraw[(int64_t)i * m + q] : 0.0;
-    }
-    __syncthreads();
-    const double mu = sw_power(k, H, z, z2);
-    __syncthreads();
-    const bool ok = sw_lu(k, H, piv);
-    if (ok) {
-        for (int i = ln; i < k; i += kSW) z[i] = 1.0 / sqrt((double)k);
-        __syncthreads();
-        for (int it = 0; it < kKI; ++it) {
-            sw_lu_solve(k, H, piv, z);
-            double ss = 0;
-            for (int i = ln; i < k; i += kSW) ss += z[i] * z[i];
-            const double nz = sqrt(sw_sum(ss));
-            __syncthreads();
-            for (int i = ln; i < k; i += kSW) z[i] /= nz;
-            __syncthreads();
+    const int q0 = ln < k ? ln : k - 1, q1 = ln + kWave < k ? ln + kWave : k - 1;
+    for (int i0 = (threadIdx.x / kWave) * 8; i0 < k; i0 += 16) {
+        double v0[8], v1[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int i = min(i0 + e, k - 1);
+            v0[e] = Hraw[(int64_t)i * m + max(q0, i - 1)];
+            v1[e] = Hraw[(int64_t)i * m + max(q1, i - 1)];
         }
-        for (int i = ln; i < k; i += kSW) zc[i] = z[i] * vscale[i];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int i = min(i0 + e, k - 1);
+            H[q0 * kRL + i] = i <= q0 + 1 ? v0[e] : 0.0;
+            H[q1 * kRL + i] = i <= q1 + 1 ? v1[e] : 0.0;
+        }
     }
-    if (ln == 0) {
-        st->mu = mu;
-        st->ok = ok ? 1 : 0;
+    if (threadIdx.x < 8) zs[kRP + threadIdx.x] = 0.0;
+    if (threadIdx.x < kRP) zs[threadIdx.x] = 0.0;
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+        const double mu = ritz_power(k, H, zp);
+        if (ln == 0) st->mu = mu;
+        return;
     }
+    unsigned long long ex[2];
+    const bool ok = ritz_lu(k, H, U, inv, lm, ex);
+    if (ok) {
+        double z0 = ln < k ? 1.0 / sqrt((double)k) : 0.0, z1 = ln + kWave < k ? 1.0 / sqrt((double)k) : 0.0;
+        const double i0 = ln < k ? inv[ln] : 0.0, i1 = ln + kWave < k ? inv[ln + kWave] : 0.0;
+        for (int it = 0; it < kKI; ++it) {
+            ritz_solve(k, U, i0, i1, lm, ex, zs, z0, z1);
+            const double nz = sqrt(gwave_sum(z0 * z0 + z1 * z1));
+            z0 /= nz;
+            z1 /= nz;
+        }
+        if (ln < k) zc[ln] = z0 * vscale[ln];
+        if (ln + kWave < k) zc[ln + kWave] = z1 * vscale[ln + kWave];
+    }
+    if (ln == 0) st->ok = ok ? 1 : 0;
 }
 
 // ||u||: slot 0 of the partials; the candidate is kept when ||u|| > 1e-8.
@@ -589,7 +783,7 @@ void adapt_cycle_end(const EngineArgs& e, const double* V, const double* coef) {
     k_ucoef<<<1, kUC, 0, st>>>(a.st, 1, 0, a.part, NB, a.C, ld, a.s, nullptr, e.ctrl, 1);
     k_uaxpy<<<NB, kWG, 0, st>>>(e.n, e.ldv, a.U, a.st, a.s, a.dvec, e.xh, e.ctrl, 1);
     // Ritz vector u = V_k z of the smallest eigenvalue of H_k, |mu|.
-    k_ritz<<<1, kSW, 0, st>>>(e.m, e.Hraw, e.vscale, a.st, a.zc, e.ctrl, 1);
+    k_ritz<<<1, 2 * kWave, 0, st>>>(e.m, e.Hraw, e.vscale, a.st, a.zc, e.ctrl, 1);
     k_vcomb<<<NB, kWG, 0, st>>>(e.n, e.ldv, V, a.zc, a.ucand, e.ctrl, 1);
     // Classical Gram-Schmidt against U, twice.
     for (int pass = 0; pass < 2; ++pass) {

@@ -79,62 +79,6 @@ __device__ __forceinline__ int64_t uni64(int64_t x) {
 __device__ __forceinline__ double unid(double x) { return __longlong_as_double(uni64(__double_as_longlong(x))); }
 
 // ------------------------------------------------------------ wave reductions
-template <int CTRL>
-__device__ __forceinline__ float gdpp(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-template <int CTRL>
-__device__ __forceinline__ double gdpp(double v) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffull), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-// a <- [a.lower half, b.lower half], b <- [a.upper half, b.upper half] (32
-// lanes each); the 16-lane form does the same on the halves of every 32 lanes.
-__device__ __forceinline__ void swap32(unsigned& a, unsigned& b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-}
-__device__ __forceinline__ void swap16(unsigned& a, unsigned& b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-}
-template <bool HALF32>
-__device__ __forceinline__ float swap_add(float x, float y) {
-    unsigned a = __float_as_uint(x), b = __float_as_uint(y);
-    if (HALF32) swap32(a, b);
-    else swap16(a, b);
-    return __uint_as_float(a) + __uint_as_float(b);
-}
-template <bool HALF32>
-__device__ __forceinline__ double swap_add(double x, double y) {
-    const unsigned long long ux = (unsigned long long)__double_as_longlong(x);
-    const unsigned long long uy = (unsigned long long)__double_as_longlong(y);
-    unsigned a0 = (unsigned)ux, a1 = (unsigned)(ux >> 32), b0 = (unsigned)uy, b1 = (unsigned)(uy >> 32);
-    if (HALF32) {
-        swap32(a0, b0);
-        swap32(a1, b1);
-    } else {
-        swap16(a0, b0);
-        swap16(a1, b1);
-    }
-    return __longlong_as_double((long long)(((unsigned long long)a1 << 32) | a0)) +
-           __longlong_as_double((long long)(((unsigned long long)b1 << 32) | b0));
-}
-
-// Sum over the 64 lanes, valid in every lane.
-template <typename T>
-__device__ __forceinline__ T gwave_sum(T v) {
-    v += gdpp<0xB1>(v);
-    v += gdpp<0x4E>(v);
-    v += gdpp<0x141>(v);
-    v += gdpp<0x140>(v);
-    v = swap_add<false>(v, v);
-    return swap_add<true>(v, v);
-}
 // Sum over aligned groups of G lanes (G a power of two <= 64), every lane.
 template <typename T>
 __device__ __forceinline__ T ggroup_sum(T v, int G) {
