@@ -322,16 +322,6 @@ __device__ void sw_lu_solve(int k, const double* LU, const int* piv, double* z) 
 // single-wavefront form, 105 us now.
 constexpr int kRL = kMaxM + 1;   // column stride in LDS (odd: rows and columns without conflicts)
 
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-__device__ __forceinline__ double lane_value(double v, int lane) {   // lane: uniform
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, lane);
-    const unsigned hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), lane);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
 __device__ __forceinline__ double entry(double v0, double v1, int p) {   // p: uniform
     return p < kWave ? lane_value(v0, p) : lane_value(v1, p - kWave);
 }

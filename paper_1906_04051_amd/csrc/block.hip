@@ -54,6 +54,12 @@ __device__ __forceinline__ d4 mfma16(double a, double b, d4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// Rows n .. n_pad - 1 of three panels that follow each other (stride ps).
+__global__ __launch_bounds__(kWG) void k_bpad(int64_t n, int64_t n_pad, int pw, int64_t ps, double* __restrict__ P) {
+    const int cnt = (int)(n_pad - n) * pw;
+    for (int e = threadIdx.x; e < 3 * cnt; e += kWG) P[e / cnt * ps + n * pw + e % cnt] = 0.0;
+}
+
 // Row-major n x k (caller layout) <-> panel of pw columns (pw = 8 or 16,
 // k <= pw; rows of pw doubles).
 __global__ __launch_bounds__(kWG) void k_bpack(int64_t n, int k, int pw, const double* __restrict__ src,
@@ -255,6 +261,7 @@ __global__ __launch_bounds__(kWG) void k_bcolsum(int nblk, const double* __restr
     __shared__ double red[kWG];
     const int c = threadIdx.x & (kBW - 1), s = threadIdx.x / kBW;
     double acc = 0.0;
+#pragma unroll 16
     for (int b = s; b < nblk; b += kWG / kBW) acc += part[(int64_t)b * kBW + c];
     red[threadIdx.x] = acc;
     __syncthreads();
@@ -597,80 +604,78 @@ __global__ __launch_bounds__(kWG) void k_bgemm_gram(int64_t n_pad, int64_t ps, c
 // a pivot <= kBdTol times the column's norm before orthogonalisation
 // (sqrt(nb2[c]), else sqrt(G_cc)) sets *flag |= 2, bdmask[c] = 1, and makes
 // row c of R and of R^{-1} zero (the column counts as dependent).
-__global__ void k_bchol(int k, const double* __restrict__ G, const double* __restrict__ nb2, int test,
-                        const double* __restrict__ Rprev, double* __restrict__ Rout,
-                        double* __restrict__ Rinv, int* flag, int* __restrict__ bdmask,
-                        const int* __restrict__ stop) {
+//
+// One wavefront, bound by the latency of its chain of k pivots: lane l holds
+// rows 4 (l/16) .. + 3 of column l%16 in registers, a pivot is a lane
+// broadcast, and only the pivot row goes through LDS; the inverse is one
+// column a lane with R's entries broadcast from LDS.  20.3 us at k = 16 and
+// 15.8 us at k = 5 with the matrices in LDS and a barrier a pivot;
+// 12.0 and 7.5 us now.
+__global__ __launch_bounds__(kWave) void k_bchol(int k, const double* __restrict__ G,
+                                                 const double* __restrict__ nb2, int test,
+                                                 const double* __restrict__ Rprev, double* __restrict__ Rout,
+                                                 double* __restrict__ Rinv, int* flag,
+                                                 int* __restrict__ bdmask, const int* __restrict__ stop) {
     if (stop && *stop) return;   // a later step of a cycle that has ended
-    __shared__ double R[kPan], Ri[kPan], Gs[kPan], Rp[kPan], nbs[kBW];
-    __shared__ int bd[kBW];
-    const int t = threadIdx.x;   // 64 threads; t < 16 active in the triangular loops
-    // Every input is read into LDS once, before the dependent loops.
-    if (t < kBW) {
-        bd[t] = 0;
-        nbs[t] = nb2 ? nb2[t] : 0.0;
+    __shared__ __align__(16) double R[kPan], Rp[kPan];
+    const int l = threadIdx.x, c = l & (kBW - 1), r0 = (l / kBW) * 4;
+    double a[4], diag[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        a[e] = (r0 + e < k && c < k) ? G[(r0 + e) * kBW + c] : 0.0;
+        diag[e] = a[e];
+        Rp[(r0 + e) * kBW + c] = Rprev ? Rprev[(r0 + e) * kBW + c] : 0.0;
+        R[(r0 + e) * kBW + c] = r0 + e == c ? 1.0 : 0.0;
     }
-    for (int e = t; e < kPan; e += blockDim.x) {
-        R[e] = 0.0;
-        Ri[e] = 0.0;
-        Gs[e] = G[e];
-        Rp[e] = Rprev ? Rprev[e] : 0.0;
-    }
-    __syncthreads();
+    const double nbl = nb2 ? nb2[c] : 0.0;
+    unsigned bd = 0;
+    wave_lds_sync();
+#pragma unroll
     for (int j = 0; j < kBW; ++j) {
-        if (t == 0) {
-            double d;
-            if (j >= k) {
-                d = 1.0;
-            } else {
-                double p = Gs[j * kBW + j];
-                for (int i = 0; i < j; ++i) p -= R[i * kBW + j] * R[i * kBW + j];
-                const double before = nb2 ? nbs[j] : Gs[j * kBW + j];
-                if (test && !(p > kBdTol * kBdTol * before)) bd[j] = 1;
-                // A broken column counts as dependent: zero row of R.
-                d = (p > 0.0 && !bd[j]) ? sqrt(p) : 0.0;
-            }
-            R[j * kBW + j] = d;
-        }
-        __syncthreads();
-        if (t > j && t < kBW) {
-            double s = (j < k && t < k) ? Gs[j * kBW + t] : 0.0;
-            for (int i = 0; i < j; ++i) s -= R[i * kBW + j] * R[i * kBW + t];
-            const double d = R[j * kBW + j];
-            R[j * kBW + t] = d > 0.0 ? s / d : 0.0;
-        }
-        __syncthreads();
+        if (j >= k) break;
+        const int gl = (j / 4) * kBW;   // first lane of the pivot row's group
+        const double p = lane_value(a[j % 4], gl + j);
+        const double before = nb2 ? lane_value(nbl, j) : lane_value(diag[j % 4], gl + j);
+        // A broken column counts as dependent: zero row of R.
+        if (test && !(p > kBdTol * kBdTol * before)) bd |= 1u << j;
+        const double d = (p > 0.0 && !((bd >> j) & 1)) ? sqrt(p) : 0.0;
+        const double row = c == j ? d : (c > j && d > 0.0) ? a[j % 4] / d : 0.0;
+        if (l / kBW == j / 4) R[j * kBW + c] = row;
+        wave_lds_sync();
+        const double rc = R[j * kBW + c];
+        // Rows up to j are finished: what this leaves there is not used.
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] -= R[j * kBW + r0 + e] * rc;
     }
-    // Column t of R^{-1} by back substitution (broken pivots give zeros).
-    if (t < kBW) {
-        for (int i = kBW - 1; i >= 0; --i) {
-            double s = i == t ? 1.0 : 0.0;
-            for (int q = i + 1; q < kBW; ++q) s -= R[i * kBW + q] * Ri[q * kBW + t];
-            const double d = R[i * kBW + i];
-            Ri[i * kBW + t] = (d > 0.0 && !bd[i]) ? s / d : 0.0;
+    // Column c of R^{-1} by back substitution (broken pivots give zeros).
+    double x[kBW];
+#pragma unroll
+    for (int i = kBW - 1; i >= 0; --i) {
+        double s = i == c ? 1.0 : 0.0;
+#pragma unroll
+        for (int q = i + 1; q < kBW; ++q) s -= R[i * kBW + q] * x[q];
+        const double d = R[i * kBW + i];
+        x[i] = s;
+        if (i < k) x[i] = d > 0.0 ? s / d : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < kBW; ++i)
+        if (l / kBW == i / 4) Rinv[i * kBW + c] = x[i];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int i = r0 + e;
+        double o = 0.0;
+        if (Rprev) {
+#pragma unroll
+            for (int q = 0; q < kBW; ++q)
+                if (q >= i && q <= c) o += R[i * kBW + q] * Rp[q * kBW + c];
+        } else {
+            o = R[i * kBW + c];
         }
+        Rout[i * kBW + c] = o;
     }
-    __syncthreads();
-    if (t < kBW) {
-        for (int i = 0; i < kBW; ++i) {
-            double o;
-            if (Rprev) {
-                o = 0.0;
-                for (int q = i; q <= t; ++q) o += R[i * kBW + q] * Rp[q * kBW + t];
-            } else {
-                o = R[i * kBW + t];
-            }
-            Rout[i * kBW + t] = o;
-            Rinv[i * kBW + t] = Ri[i * kBW + t];
-        }
-    }
-    __syncthreads();
-    if (t < kBW && test && bdmask) bdmask[t] = bd[t];
-    if (t == 0 && test) {
-        int any = 0;
-        for (int j = 0; j < kBW; ++j) any |= bd[j];
-        if (any) *flag |= 2;
-    }
+    if (test && bdmask && l < kBW) bdmask[l] = (bd >> l) & 1;
+    if (test && bd && l == 0) *flag |= 2;
 }
 
 // In-place column selection of a panel: column i <- column map[i] (map[i] < 0:
@@ -721,6 +726,12 @@ __global__ __launch_bounds__(kWG) void k_bls_init(int kb, int ka, const double* 
 // side's residual.  flag[0] |= 1 when every one passes.  It ends the block
 // step: flag[2] counts the cycle's steps, and flag[1] (the gate of every later
 // kernel of the cycle) is set once flag[0] is (this step ended the cycle).
+//
+// One workgroup, bound by the latency of the chain of reflectors (j k earlier
+// ones, k new ones): sixteen lanes a column, entries in registers that move
+// along the lanes, sums on the vector unit, one barrier a new reflector.
+// k = 16, steps 1 to 8: 41 us on average with the columns in LDS and shuffled
+// sums, 28 us now.
 __global__ __launch_bounds__(kWG) void k_bls(int j, int k, int ka, double rtol,
                                              const double* __restrict__ Csum,
                                              const double* __restrict__ Rj, LsView ls, int* flag) {
@@ -730,18 +741,13 @@ __global__ __launch_bounds__(kWG) void k_bls(int j, int k, int ka, double rtol,
     __shared__ double h[kBW][kLdH + 1];
     __shared__ double vl[(kBlockStepsMax - 1) * kBW * (kBW + 1)];   // previous reflectors
     __shared__ double bl[(kBlockStepsMax - 1) * kBW];
-    __shared__ double vs[kBW + 1];
-    __shared__ double bs;
-    // Rows c0 .. c0 + 2k - 1 of the right-hand sides' columns of G: the only
-    // rows this step's reflectors touch, kept in LDS until the end.
-    __shared__ double gl[kBW][2 * kBW + 1];
+    __shared__ double col[2][kBW + 1];   // the column whose reflector is made
     __shared__ double est2[kBW];
     const int t = threadIdx.x;
     const int rows = (j + 2) * k, c0 = j * k;
-    for (int e = t; e < kBW * 2 * kBW; e += kWG) {
-        const int c = e / (2 * kBW), r = e % (2 * kBW);
-        gl[c][r] = (c < ka && r < 2 * k) ? ls.G[(int64_t)c * kLdH + c0 + r] : 0.0;
-    }
+    const int ct = t / kBW, li = t & (kBW - 1);
+    // Rows c0 .. c0 + k - 1 of G; the rows below are still zero.
+    double gw = (ct < ka && li < k) ? ls.G[(int64_t)ct * kLdH + c0 + li] : 0.0, gx = 0.0;
     // Every global load of the inputs is issued before the first is stored
     // to LDS (fixed trip counts, registers in between).
     constexpr int kVIt = ((kBlockStepsMax - 1) * kBW * (kBW + 1) + kWG - 1) / kWG;
@@ -776,110 +782,66 @@ __global__ __launch_bounds__(kWG) void k_bls(int j, int k, int ka, double rtol,
         if (e < kBW * kLdH) h[e / kLdH][e % kLdH] = hr[u];
     }
     __syncthreads();
-    // Previous reflectors, in order, on every column of the new block: 16
-    // lanes per column, lane i holding entry p + i of reflector p's window
-    // (lane 0 also entry p + 16 when k = 16); the dot product by shuffles
-    // inside the 16-lane group.  Each group walks its own column, so the
-    // groups need no barrier between reflectors.
-    {
-        const int ct = t / kBW, li = t & (kBW - 1);
-        if (ct < k) {
-            for (int p = 0; p < c0; ++p) {
-                const double* vp = vl + p * (kBW + 1);
-                const double v0 = li <= k ? vp[li] : 0.0;
-                const double v16 = (li == 0 && k == kBW) ? vp[kBW] : 0.0;
-                const double h0 = h[ct][p + li];
-                const double h16 = (li == 0 && k == kBW) ? h[ct][p + kBW] : 0.0;
-                double part = v0 * h0 + v16 * h16;
-#pragma unroll
-                for (int o = kBW / 2; o > 0; o >>= 1) part += __shfl_xor(part, o, kBW);
-                const double sp = part * bl[p];
-                if (li <= k) h[ct][p + li] = h0 - sp * v0;
-                if (li == 0 && k == kBW) h[ct][p + kBW] = h16 - sp * v16;
-            }
-        }
+    // Sixteen lanes hold a column's window: lane i entry p + i, lane 0 also
+    // entry p + 16 (x).  After reflector p the window moves down by one: entry
+    // p is final, and entry p + 16 enters at lane 15.
+    double w = h[ct][li], x = h[ct][kBW];
+    for (int p = 0; p < c0; ++p) {
+        const double v0 = li <= k ? vl[p * (kBW + 1) + li] : 0.0;
+        const double v16 = k == kBW ? vl[p * (kBW + 1) + kBW] : 0.0;
+        const double nx = h[ct][p + kBW + 1];
+        const double sp = ggroup_sum(v0 * w + (li == 0 ? v16 * x : 0.0), kBW) * bl[p];
+        w -= sp * v0;
+        x -= sp * v16;
+        if (li == 0 && ct < k) ls.H[(int64_t)(c0 + ct) * kLdH + p] = w;
+        w = gdpp<0x12F>(li == 0 ? x : w);
+        x = nx;
     }
-    __syncthreads();
-    // New reflectors, one per column of the block, each built by the first
-    // 16 lanes (entries as above, norms by shuffles) and applied to the
-    // block's later columns and to the right-hand sides by 16-lane groups.
-    const int ct = t / kBW, li = t & (kBW - 1);
+    // New reflectors: column q's window goes to LDS, every group forms its
+    // reflector and applies it to its own column and right-hand side.
     for (int q = 0; q < k; ++q) {
-        const int col = c0 + q;
-        if (t < kBW) {
-            const double x0 = li <= k ? h[q][col + li] : 0.0;
-            const double x16 = (li == 0 && k == kBW) ? h[q][col + kBW] : 0.0;
-            double n2 = x0 * x0 + x16 * x16;
-#pragma unroll
-            for (int o = kBW / 2; o > 0; o >>= 1) n2 += __shfl_xor(n2, o, kBW);
-            const double nrm = sqrt(n2);
-            const double a0 = __shfl(x0, 0, kBW);
-            const double alpha = a0 >= 0.0 ? -nrm : nrm;
-            const double w0 = nrm > 0.0 ? (li == 0 ? a0 - alpha : x0) : 0.0;
-            const double w16 = nrm > 0.0 ? x16 : 0.0;
-            double vv = w0 * w0 + w16 * w16;
-#pragma unroll
-            for (int o = kBW / 2; o > 0; o >>= 1) vv += __shfl_xor(vv, o, kBW);
-            const double beta = (nrm > 0.0 && vv > 0.0) ? 2.0 / vv : 0.0;
-            if (li <= k) {
-                vs[li] = w0;
-                ls.v[(int64_t)col * (kBW + 1) + li] = w0;
-            }
-            if (li == 0 && k == kBW) {
-                vs[kBW] = w16;
-                ls.v[(int64_t)col * (kBW + 1) + kBW] = w16;
-            }
+        double* cq = col[q & 1];
+        if (ct == q) {
+            cq[li] = w;
+            if (li == 0) cq[kBW] = x;
+        }
+        __syncthreads();
+        const double a0 = cq[0], x0 = li <= k ? cq[li] : 0.0, x16 = k == kBW ? cq[kBW] : 0.0;
+        const double nrm = sqrt(ggroup_sum(x0 * x0 + (li == 0 ? x16 * x16 : 0.0), kBW));
+        const double alpha = a0 >= 0.0 ? -nrm : nrm;
+        const double v0 = nrm > 0.0 ? (li == 0 ? a0 - alpha : x0) : 0.0;
+        const double v16 = nrm > 0.0 ? x16 : 0.0;
+        const double vv = ggroup_sum(v0 * v0 + (li == 0 ? v16 * v16 : 0.0), kBW);
+        const double beta = (nrm > 0.0 && vv > 0.0) ? 2.0 / vv : 0.0;
+        if (ct == 0) {
+            if (li <= k) ls.v[(int64_t)(c0 + q) * (kBW + 1) + li] = v0;
             if (li == 0) {
-                bs = beta;
-                ls.beta[col] = beta;
+                if (k == kBW) ls.v[(int64_t)(c0 + q) * (kBW + 1) + kBW] = v16;
+                ls.beta[c0 + q] = beta;
             }
         }
-        __syncthreads();
-        const double beta = bs;
         if (beta != 0.0) {
-            const double v0 = li <= k ? vs[li] : 0.0;
-            const double v16 = (li == 0 && k == kBW) ? vs[kBW] : 0.0;
-            // Columns q.. of the block.
-            if (q + ct < k) {
-                const int cc = q + ct;
-                const double h0 = h[cc][col + li];
-                const double h16 = (li == 0 && k == kBW) ? h[cc][col + kBW] : 0.0;
-                double sp = v0 * h0 + v16 * h16;
-#pragma unroll
-                for (int o = kBW / 2; o > 0; o >>= 1) sp += __shfl_xor(sp, o, kBW);
-                sp *= beta;
-                if (li <= k) h[cc][col + li] = h0 - sp * v0;
-                if (li == 0 && k == kBW) h[cc][col + kBW] = h16 - sp * v16;
-            }
-            // Right-hand sides (rows q .. q + k of the staged block).
-            if (ct < ka) {
-                const double g0 = q + li < 2 * kBW ? gl[ct][q + li] : 0.0;
-                const double g16 = (li == 0 && k == kBW) ? gl[ct][q + kBW] : 0.0;
-                double sp = v0 * g0 + v16 * g16;
-#pragma unroll
-                for (int o = kBW / 2; o > 0; o >>= 1) sp += __shfl_xor(sp, o, kBW);
-                sp *= beta;
-                if (li <= k) gl[ct][q + li] = g0 - sp * v0;
-                if (li == 0 && k == kBW) gl[ct][q + kBW] = g16 - sp * v16;
-            }
+            const double sp = ggroup_sum(v0 * w + (li == 0 ? v16 * x : 0.0), kBW) * beta;
+            const double sg = ggroup_sum(v0 * gw + (li == 0 ? v16 * gx : 0.0), kBW) * beta;
+            w -= sp * v0;
+            x -= sp * v16;
+            gw -= sg * v0;
+            gx -= sg * v16;
         }
-        __syncthreads();
-    }
-    for (int e = t; e < k * rows; e += kWG) {
-        const int col = e / rows, row = e % rows;
-        ls.H[(int64_t)(c0 + col) * kLdH + row] = h[col][row];
-    }
-    for (int e = t; e < kBW * 2 * kBW; e += kWG) {
-        const int c = e / (2 * kBW), r = e % (2 * kBW);
-        if (c < ka && r < 2 * k) ls.G[(int64_t)c * kLdH + c0 + r] = gl[c][r];
+        if (li == 0) {
+            if (ct >= q && ct < k) ls.H[(int64_t)(c0 + ct) * kLdH + c0 + q] = w;
+            if (ct < ka) ls.G[(int64_t)ct * kLdH + c0 + q] = gw;
+        }
+        w = gdpp<0x12F>(li == 0 ? x : w);
+        x = h[ct][min(c0 + q + kBW + 1, kLdH - 1)];   // past the block's rows: zero
+        gw = gdpp<0x12F>(li == 0 ? gx : gw);
+        gx = 0.0;
     }
     // Residual estimate of each right-hand side: the norm of its transformed
-    // rows (j+1)k .. (j+2)k-1 (rows k .. 2k-1 of the staged block).
-    if (t < ka) {
-        double e2 = 0.0;
-        for (int i = k; i < 2 * k; ++i) e2 += gl[t][i] * gl[t][i];
-        est2[t] = e2;
-    }
+    // rows (j+1)k .. (j+2)k-1, now in the window.
+    if (ct < ka && li < k) ls.G[(int64_t)ct * kLdH + c0 + k + li] = gw;
+    const double e2 = ggroup_sum(li < k ? gw * gw : 0.0, kBW);
+    if (li == 0) est2[ct] = e2;
     __syncthreads();
     if (t == 0) {
         int conv = 1;
@@ -897,9 +859,12 @@ __global__ __launch_bounds__(kWG) void k_bls(int j, int k, int ka, double rtol,
 
 // Y = R^{-1} G_top (R: leading J x J upper triangle of H, J = nblk * k; ka
 // right-hand sides), written as nblk padded 16x16 coefficient blocks
-// Cy[blk * 256 + kk * 16 + c].
+// Cy[blk * 256 + kk * 16 + c].  One workgroup, bound by the chain of J rows:
+// three barriers per strip of eight rows, whose small triangle is solved in
+// registers.  J = 128: 82 us with two barriers a row, 39 us now.
 __global__ __launch_bounds__(kWG) void k_bsolve(int nblk, int k, int ka, LsView ls, double* __restrict__ Cy) {
     constexpr int kStrip = 8;   // rows of H staged in LDS at a time
+    constexpr int kLd = (kStrip * kBlockStepsMax * kBW) / kWG;
     __shared__ double y[kLdH][kBW];
     __shared__ double part[kBW][kBW + 1];
     __shared__ double hs[kStrip][kBlockStepsMax * kBW + 1];
@@ -908,28 +873,49 @@ __global__ __launch_bounds__(kWG) void k_bsolve(int nblk, int k, int ka, LsView 
     // y starts as the right-hand side G; row i is overwritten by the solution
     // once the rows below it are solved.
     for (int e = threadIdx.x; e < kLdH * kBW; e += kWG) {
-        const int i = e / kBW, cc = e % kBW;
+        const int i = e % kLdH, cc = e / kLdH;
         y[i][cc] = i < J ? ls.G[(int64_t)cc * kLdH + i] : 0.0;
     }
-    for (int i0 = (J - 1) / kStrip * kStrip; i0 >= 0 && J > 0; i0 -= kStrip) {
-        __syncthreads();   // the previous strip is done with hs
-        for (int e = threadIdx.x; e < kStrip * J; e += kWG) {
-            const int q = e / kStrip, r = e % kStrip;
-            hs[r][q] = i0 + r < J ? ls.H[(int64_t)q * kLdH + i0 + r] : 0.0;
+    double ld[kLd];   // the next strip, in flight
+    auto load = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < kLd; ++u) {
+            const int e = threadIdx.x + u * kWG, q = e / kStrip, r = e % kStrip;
+            ld[u] = (i0 >= 0 && q < J && i0 + r < J && q >= i0 + r) ? ls.H[(int64_t)q * kLdH + i0 + r] : 0.0;
+        }
+    };
+    const int last = (J - 1) / kStrip * kStrip;
+    if (J > 0) load(last);
+    for (int i0 = last; i0 >= 0 && J > 0; i0 -= kStrip) {
+        __syncthreads();   // the previous strip is done with hs and y
+#pragma unroll
+        for (int u = 0; u < kLd; ++u) {
+            const int e = threadIdx.x + u * kWG;
+            hs[e % kStrip][e / kStrip] = ld[u];
+        }
+        load(i0 - kStrip);
+        __syncthreads();
+        // The strip's rows less the solved ones' products: two groups a row.
+        {
+            double s = 0.0;
+#pragma unroll 4
+            for (int q = i0 + kStrip + (g & 1); q < J; q += 2) s += hs[g / 2][q] * y[q][c];
+            part[g][c] = s;
         }
         __syncthreads();
-        for (int i = min(J - 1, i0 + kStrip - 1); i >= i0; --i) {
-            double s = 0.0;
-            if (c < ka)
-                for (int q = i + 1 + g; q < J; q += kBW) s += hs[i - i0][q] * y[q][c];
-            part[g][c] = s;
-            __syncthreads();
-            if (g == 0 && c < ka) {
-                double acc = y[i][c];
-                for (int q = 0; q < kBW; ++q) acc -= part[q][c];
-                y[i][c] = acc / hs[i - i0][i];
+        if (g == 0) {
+            double yy[kStrip];
+#pragma unroll
+            for (int r = kStrip - 1; r >= 0; --r) {
+                yy[r] = 0.0;
+                if (i0 + r < J) {
+                    double acc = y[i0 + r][c] - part[2 * r][c] - part[2 * r + 1][c];
+#pragma unroll
+                    for (int q = r + 1; q < kStrip; ++q) acc -= hs[r][i0 + q] * yy[q];
+                    yy[r] = c < ka ? acc / hs[r][i0 + r] : 0.0;
+                    y[i0 + r][c] = yy[r];
+                }
             }
-            __syncthreads();
         }
     }
     __syncthreads();
@@ -1067,9 +1053,7 @@ int block_bind(BlockWork* w, void* mem, size_t bytes, hipStream_t st, int64_t n,
     ar.cap = bytes;
     block_carve(w, ar, n, m);
     if (ar.short_ || (ar.base & 255) != 0) return kStatusNoMem;
-    // Panel rows beyond n and columns beyond k stay zero through the solve.
-    if (hipMemsetAsync(w->panels, 0, (size_t)(m + 4) * w->ps * sizeof(double), st) != hipSuccess ||
-        hipMemsetAsync(w->lsbuf, 0, (size_t)ls_entries() * sizeof(double), st) != hipSuccess)
+    if (hipMemsetAsync(w->lsbuf, 0, (size_t)ls_entries() * sizeof(double), st) != hipSuccess)
         return kStatusDevice;
     double* q = w->lsbuf;
     w->ls.H = q;
@@ -1319,6 +1303,10 @@ int block_solve(BlockWork* w, const BlockArgs& a, BlockResult* res) {
     w->ps = w->n_pad * w->pw;
     const int64_t pe = w->n * w->pw;
     const unsigned gpe = (unsigned)((pe + kWG - 1) / kWG);
+    // Panel rows beyond n and columns beyond k stay zero through the solve:
+    // set here for W, B and X; a basis panel is written whole, from W, before
+    // it is read (clearing all panels took 0.27 ms at 1,050,625 rows, m = 8).
+    if (w->n_pad > w->n) k_bpad<<<1, kWG, 0, st>>>(w->n, w->n_pad, w->pw, w->ps, w->W());
     k_bpack<<<gpe, kWG, 0, st>>>(w->n, k, w->pw, a.B, w->Bp());
     k_bpack<<<gpe, kWG, 0, st>>>(w->n, k, w->pw, a.X0, w->Xp());
     // rho0_c = ||b_c - A x0_c|| (unprojected); the tests use ||P (b_c - A x_c)||.

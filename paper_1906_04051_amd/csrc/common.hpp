@@ -137,6 +137,19 @@ __device__ __forceinline__ double swap_add(double x, double y) {
            __longlong_as_double((long long)(((unsigned long long)b1 << 32) | b0));
 }
 
+// Value of a lane (the same one for the whole wavefront), in scalar registers.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, lane);
+    const unsigned hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// Orders a wavefront's own LDS accesses.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Sum over the 64 lanes, valid in every lane.
 template <typename T>
 __device__ __forceinline__ T gwave_sum(T v) {
@@ -146,6 +159,17 @@ __device__ __forceinline__ T gwave_sum(T v) {
     v += gdpp<0x140>(v);
     v = swap_add<false>(v, v);
     return swap_add<true>(v, v);
+}
+// Sum over aligned groups of G lanes (G a power of two <= 64), every lane.
+template <typename T>
+__device__ __forceinline__ T ggroup_sum(T v, int G) {
+    if (G >= 2) v += gdpp<0xB1>(v);
+    if (G >= 4) v += gdpp<0x4E>(v);
+    if (G >= 8) v += gdpp<0x141>(v);
+    if (G >= 16) v += gdpp<0x140>(v);
+    if (G >= 32) v = swap_add<false>(v, v);
+    if (G >= 64) v = swap_add<true>(v, v);
+    return v;
 }
 
 // Sum over a workgroup of kWG threads; result valid in every thread.

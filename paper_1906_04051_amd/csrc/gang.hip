@@ -79,17 +79,6 @@ __device__ __forceinline__ int64_t uni64(int64_t x) {
 __device__ __forceinline__ double unid(double x) { return __longlong_as_double(uni64(__double_as_longlong(x))); }
 
 // ------------------------------------------------------------ wave reductions
-// Sum over aligned groups of G lanes (G a power of two <= 64), every lane.
-template <typename T>
-__device__ __forceinline__ T ggroup_sum(T v, int G) {
-    if (G >= 2) v += gdpp<0xB1>(v);
-    if (G >= 4) v += gdpp<0x4E>(v);
-    if (G >= 8) v += gdpp<0x141>(v);
-    if (G >= 16) v += gdpp<0x140>(v);
-    if (G >= 32) v = swap_add<false>(v, v);
-    if (G >= 64) v = swap_add<true>(v, v);
-    return v;
-}
 // Sums of eight values over the wavefront: halving exchanges (32, 16, 8 lanes)
 // leave lane l with the sum of value ((l >> 3) & 1) + 2 ((l >> 4) & 1) +
 // 4 (l >> 5): ten exchanges instead of 48.

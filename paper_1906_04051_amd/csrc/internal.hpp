@@ -463,7 +463,7 @@ struct BlockResult {
     double rho0 = 0.0, rel_res_est = 0.0, rel_res_true = 0.0;
 };
 // Block workspace carved from caller memory of block_workspace_bytes(n, m)
-// bytes (256-byte aligned).  block_bind zeroes the panels.
+// bytes (256-byte aligned).  The panels need no clearing.
 struct BlockWork;
 size_t block_workspace_bytes(int64_t n, int m);
 int block_bind(BlockWork* w, void* mem, size_t bytes, hipStream_t st, int64_t n, int m);
