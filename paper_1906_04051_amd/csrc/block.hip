@@ -198,58 +198,118 @@ __global__ __launch_bounds__(kWG) void k_bnorm(int64_t n, int pw, const double* 
 }
 
 // Y = A X (MODE 0), or Y = B - A X with per-workgroup partial sums of squares
-// of every column (MODE 1).  16 lanes per row, 16 rows per workgroup.
+// of every column (MODE 1).  PW / 2 lanes per row, two columns each; a
+// wavefront takes 64 / (PW / 2) rows a round, a workgroup one contiguous range
+// of rows, and each die a contiguous range of workgroups, so the three mesh
+// lines a row gathers from meet in one L2.  What bounds it is the rate at
+// which addresses are processed (16 cycles a load, whatever it reads): the
+// lanes of a row would all load its column and value, 18 of 29 loads a Q1 row.
+// So a wavefront loads its rows' entries once, side by side, into its part of
+// LDS, reads them from there, and gathers X with 16-byte loads; the next
+// entries are in flight meanwhile.  1,050,625 rows of 9, 16 columns: 182 us
+// (MODE 0) and 265 (MODE 1) with a column a lane and rows dealt round the dies,
+// 152 and 187 with two columns a lane, 130 and 155 with the entries staged
+// (368 MB: 75 us at the rate of a copy).
+template <int PW>
+constexpr int kSpRows = kWG / (PW / 2);
+constexpr int kSpC = 9;        // gathers in flight a lane (a whole Q1 row)
+constexpr int kSpRounds = 2;   // rounds a workgroup when there are rows enough
+
 template <int MODE, int PW>
-__global__ __launch_bounds__(kWG) void k_bspmm(int64_t n, const int* __restrict__ rowptr,
+__global__ __launch_bounds__(kWG) void k_bspmm(int64_t n, int rounds, const int* __restrict__ rowptr,
                                                const int* __restrict__ colind,
                                                const double* __restrict__ vals,
                                                const double* __restrict__ X,
                                                const double* __restrict__ B, double* __restrict__ Y,
                                                double* __restrict__ part, const int* __restrict__ stop) {
-    __shared__ double red[kWG];
+    constexpr int lpr = PW / 2, rpr = kSpRows<PW>;
+    constexpr int NL = 32 / lpr, cap = NL * kWave;   // entries a lane, a wavefront (16 a row)
+    __shared__ int sc[kWG / kWave][cap];
+    __shared__ double sv[kWG / kWave][cap];
+    __shared__ double red[2 * kWG];
     if (stop && *stop) return;   // a later step of a cycle that has ended
-    // PW lanes per row (one per panel column), kWG / PW rows per round.
-    constexpr int pw = PW, rpr = kWG / PW;
-    const int c = threadIdx.x & (pw - 1), rl = threadIdx.x / pw;
-    double nrm = 0.0;
-    for (int64_t r0 = (int64_t)blockIdx.x * rpr; r0 < n; r0 += (int64_t)gridDim.x * rpr) {
-        const int64_t row = r0 + rl;
-        if (row < n) {
-            const int q0 = rowptr[row], q1 = rowptr[row + 1];
-            double acc = 0.0;
-            int q = q0;
-            for (; q + 4 <= q1; q += 4) {
-                const int c0 = colind[q], c1 = colind[q + 1], c2 = colind[q + 2], c3 = colind[q + 3];
-                GM_DCHECK(min(min(c0, c1), min(c2, c3)) >= 0 && max(max(c0, c1), max(c2, c3)) < n,
-                          kDbgBlockCol);
-                const double a0 = vals[q], a1 = vals[q + 1], a2 = vals[q + 2], a3 = vals[q + 3];
-                const double x0 = X[(int64_t)c0 * pw + c], x1 = X[(int64_t)c1 * pw + c];
-                const double x2 = X[(int64_t)c2 * pw + c], x3 = X[(int64_t)c3 * pw + c];
-                acc += a0 * x0;
-                acc += a1 * x1;
-                acc += a2 * x2;
-                acc += a3 * x3;
-            }
-            for (; q < q1; ++q) {
-                GM_DCHECK(colind[q] >= 0 && colind[q] < n, kDbgBlockCol);
-                acc += vals[q] * X[(int64_t)colind[q] * pw + c];
-            }
-            if (MODE == 0) {
-                Y[row * pw + c] = acc;
-            } else {
-                const double y = B[row * pw + c] - acc;
-                Y[row * pw + c] = y;
-                nrm += y * y;
+    const int l = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int c = (l & (lpr - 1)) * 2;
+    double n0 = 0.0, n1 = 0.0;
+    int64_t row = (int64_t)xcd_block(blockIdx.x, gridDim.x) * rounds * rpr + wv * (kWave / lpr) + l / lpr;
+    int ec[NL];
+    double ev[NL];
+    // Entries [base, e) into registers (at most cap of them).
+    auto fetch = [&](int base, int e) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int p = u * kWave + l;
+            ec[u] = 0;
+            ev[u] = 0.0;
+            if (p < e - base) {
+                ec[u] = colind[base + p];
+                ev[u] = vals[base + p];
+                GM_DCHECK(ec[u] >= 0 && ec[u] < n, kDbgBlockCol);
             }
         }
+    };
+    // Rows past n have no entries; the bounds of this round and the next.
+    auto bound = [&](int64_t r) { return rowptr[r < n ? r : n]; };
+    int q0 = bound(row), q1 = bound(row + 1), p0 = bound(row + rpr), p1 = bound(row + rpr + 1);
+    fetch(__builtin_amdgcn_readfirstlane(q0), __builtin_amdgcn_readlane(q1, kWave - 1));
+    for (int it = 0; it < rounds; ++it, row += rpr) {
+        const int b0 = __builtin_amdgcn_readfirstlane(q0), e0 = __builtin_amdgcn_readlane(q1, kWave - 1);
+        const int b1 = __builtin_amdgcn_readfirstlane(p0), e1 = __builtin_amdgcn_readlane(p1, kWave - 1);
+        const int t0 = bound(row + 2 * rpr), t1 = bound(row + 2 * rpr + 1);
+        double s0 = 0.0, s1 = 0.0;
+        int base = b0;
+        bool more;
+        do {
+            wave_lds_sync();   // the entries before these have been read
+#pragma unroll
+            for (int u = 0; u < NL; ++u) {
+                sc[wv][u * kWave + l] = ec[u];
+                sv[wv][u * kWave + l] = ev[u];
+            }
+            wave_lds_sync();
+            more = e0 - base > cap;
+            fetch(more ? base + cap : b1, more ? e0 : it + 1 < rounds ? e1 : b1);
+            const int f = max(q0 - base, 0), t = min(q1 - base, cap);
+            for (int q = f; q < t; q += kSpC) {
+                double2 x[kSpC];
+#pragma unroll
+                for (int e = 0; e < kSpC; ++e)   // past the row: its last entry, dropped below
+                    x[e] = *reinterpret_cast<const double2*>(X + (int64_t)sc[wv][min(q + e, t - 1)] * PW + c);
+#pragma unroll
+                for (int e = 0; e < kSpC; ++e)
+                    if (q + e < t) {
+                        const double a = sv[wv][q + e];
+                        s0 += a * x[e].x;
+                        s1 += a * x[e].y;
+                    }
+            }
+            if (more) base += cap;
+        } while (more);
+        if (row < n) {
+            double2* y = reinterpret_cast<double2*>(Y + row * PW + c);
+            if (MODE == 0) {
+                *y = make_double2(s0, s1);
+            } else {
+                const double2 b = *reinterpret_cast<const double2*>(B + row * PW + c);
+                const double y0 = b.x - s0, y1 = b.y - s1;
+                *y = make_double2(y0, y1);
+                n0 += y0 * y0;
+                n1 += y1 * y1;
+            }
+        }
+        q0 = p0;
+        q1 = p1;
+        p0 = t0;
+        p1 = t1;
     }
     if (MODE == 1) {
-        red[threadIdx.x] = nrm;
+        red[2 * threadIdx.x] = n0;
+        red[2 * threadIdx.x + 1] = n1;
         __syncthreads();
         if (threadIdx.x < kBW) {
             double s = 0.0;
-            if (threadIdx.x < pw)
-                for (int i = 0; i < rpr; ++i) s += red[i * pw + threadIdx.x];
+            if (threadIdx.x < PW)
+                for (int i = 0; i < rpr; ++i) s += red[i * PW + threadIdx.x];
             part[(int64_t)blockIdx.x * kBW + threadIdx.x] = s;
         }
     }
@@ -1217,23 +1277,28 @@ double spmm_bytes(const BlockWork& w, const BlockArgs& a, int mode) {
     return 12.0 * (double)a.nnz + 4.0 * (double)(w.n + 1) + (2.0 + mode) * (double)w.n * w.pw * sizeof(double);
 }
 
-// Y = A X (mode 0) or Y = B - A X with column partial sums of squares
-// (mode 1), the instance for the solve's panel width.
-void spmm(const BlockWork& w, const BlockArgs& a, int mode, dim3 grid, hipStream_t st, const double* X,
-          const double* B, double* Y, double* part, const int* stop) {
-    const double bytes = spmm_bytes(w, a, mode);
-    if (mode == 0 && w.pw == 8)
-        blaunch(a.timer, 7, bytes, k_bspmm<0, 8>, grid, dim3(kWG), st, w.n, a.rowptr, a.colind, a.vals, X, B, Y,
-                part, stop);
-    else if (mode == 0)
-        blaunch(a.timer, 7, bytes, k_bspmm<0, kBW>, grid, dim3(kWG), st, w.n, a.rowptr, a.colind, a.vals, X, B, Y,
-                part, stop);
-    else if (w.pw == 8)
-        blaunch(a.timer, 7, bytes, k_bspmm<1, 8>, grid, dim3(kWG), st, w.n, a.rowptr, a.colind, a.vals, X, B, Y,
-                part, stop);
+// Y = A X (mode 0, up to kSpRounds
+// rounds a workgroup while kNormGrid of them are left) or Y = B - A X with column
+// partial sums of squares (mode 1, kNormGrid workgroups), the instance for the
+// solve's panel width.
+template <int MODE, int PW>
+void spmm_pw(const BlockWork& w, const BlockArgs& a, const double* X, const double* B, double* Y, double* part,
+             const int* stop) {
+    constexpr int64_t rpr = kSpRows<PW>;
+    const int64_t rounds = MODE == 0 ? std::max<int64_t>(1, std::min<int64_t>(kSpRounds, w.n / (kNormGrid * rpr)))
+                                     : (w.n + kNormGrid * rpr - 1) / (kNormGrid * rpr);
+    const int64_t grid = MODE == 0 ? (w.n + rounds * rpr - 1) / (rounds * rpr) : kNormGrid;
+    blaunch(a.timer, 7, spmm_bytes(w, a, MODE), k_bspmm<MODE, PW>, dim3((unsigned)grid), dim3(kWG), a.st, w.n,
+            (int)rounds, a.rowptr, a.colind, a.vals, X, B, Y, part, stop);
+}
+
+template <int MODE>
+void spmm(const BlockWork& w, const BlockArgs& a, const double* X, const double* B, double* Y, double* part,
+          const int* stop) {
+    if (w.pw == 8)
+        spmm_pw<MODE, 8>(w, a, X, B, Y, part, stop);
     else
-        blaunch(a.timer, 7, bytes, k_bspmm<1, kBW>, grid, dim3(kWG), st, w.n, a.rowptr, a.colind, a.vals, X, B, Y,
-                part, stop);
+        spmm_pw<MODE, kBW>(w, a, X, B, Y, part, stop);
 }
 
 // S = E^{-1} Z^T P into w.Sz (deflation basis of a).
@@ -1271,7 +1336,7 @@ void project(const BlockWork& w, const BlockArgs& a, double* W, const int* stop)
 // W = B - A X, h_raw[c] = ||w_c||; then W = P W and h_nrm[c] = ||P w_c||
 // (h_nrm = h_raw without a deflation basis).
 int residual(const BlockWork& w, const BlockArgs& a, double* h_raw, double* h_nrm) {
-    spmm(w, a, 1, dim3(kNormGrid), a.st, (const double*)w.Xp(), (const double*)w.Bp(), w.W(), w.npart, nullptr);
+    spmm<1>(w, a, w.Xp(), w.Bp(), w.W(), w.npart, nullptr);
     k_bcolsum<<<1, kWG, 0, a.st>>>(kNormGrid, w.npart, w.nsq);
     double sq[kBW], sp[kBW];
     if (hipMemcpyAsync(sq, w.nsq, sizeof(sq), hipMemcpyDeviceToHost, a.st) != hipSuccess) return kStatusDevice;
@@ -1386,8 +1451,7 @@ int block_solve(BlockWork* w, const BlockArgs& a, BlockResult* res) {
             if (a.timer) a.timer->step(j);
             double* Vj = w->V() + (int64_t)j * w->ps;
             double* Vn = w->V() + (int64_t)(j + 1) * w->ps;
-            const unsigned g16 = (unsigned)((w->n + kWG / w->pw - 1) / (kWG / w->pw));
-            spmm(*w, a, 0, dim3(g16), st, (const double*)Vj, nullptr, w->W(), nullptr, stop);
+            spmm<0>(*w, a, Vj, nullptr, w->W(), nullptr, stop);
             project(*w, a, w->W(), stop);   // W = P A V_j
             // BCGS2: two projections onto V_0..V_j; the first also gives the
             // squared column norms of A V_j (the breakdown reference).
@@ -1426,8 +1490,7 @@ int block_solve(BlockWork* w, const BlockArgs& a, BlockResult* res) {
     if (a.R > 0) {
         // x_c = x_hat_c + Z E^{-1} Z^T (b_c - A x_hat_c) (eq. precond2); the
         // true residuals are then recomputed.
-        spmm(*w, a, 1, dim3(kNormGrid), st, (const double*)w->Xp(), (const double*)w->Bp(), w->W(), w->npart,
-             nullptr);
+        spmm<1>(*w, a, w->Xp(), w->Bp(), w->W(), w->npart, nullptr);
         coarse(*w, a, w->W(), nullptr);
         zapply(*w, st, a.R, a.zrp, a.zci, a.zv, 1.0, w->Xp(), nullptr);
         if ((s = residual(*w, a, raw, rn)) != kStatusOk) return s;

@@ -19,10 +19,21 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("k,m,steps", [(4, 1, 3), (7, 5, 9), (9, 3, 6), (15, 16, 18), (16, 7, 9), (16, 16, 17)])
 def test_block_widths_match_oracle(k, m, steps):
+    _check(W.make_config(1, mesh=40), k, m, steps)   # 1,681 unknowns: 17 rows past a multiple of 64
+
+
+@pytest.mark.parametrize("k", [5, 16])
+def test_block_rows_beyond_one_stage(k):
+    """Q2 rows (9 to 25 entries): the eight (sixteen) rows of a wavefront hold
+    more entries than one stage of the SpMM."""
+    _check(W.make_config(3, mesh=20), k, 4, 6)
+
+
+def _check(s, k, m, steps):
     from paper_1906_04051_amd import gmres as G
     if not torch.cuda.is_available():
         pytest.skip("no GPU visible")
-    s = copy.copy(W.make_config(1, mesh=40))     # 1,681 unknowns: 17 rows past a multiple of 64
+    s = copy.copy(s)
     s.r = 0
     s.z_rowptr = np.zeros(s.n + 1, np.int32)
     s.z_colind = np.zeros(0, np.int32)
