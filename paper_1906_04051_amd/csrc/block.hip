@@ -335,7 +335,7 @@ __global__ __launch_bounds__(kWG) void k_bcolsum(int nblk, const double* __restr
 // Partial products C_i = P_i^T W (P_i = panel i of V for i < nv; with gram,
 // P_nv = W) over 4-row chunks, one MFMA accumulator per panel; workgroups
 // with blockIdx.y = g take panels [NG g, NG g + NG) (W is read once per
-// group, which keeps NG accumulators per lane and the occupancy high);
+// group; NG accumulators per lane);
 // per-workgroup partials part[(blockIdx.x * nb + i) * 256 + m * 16 + n]
 // (fixed order).  Panels beyond nb are loaded (W again) and multiplied but
 // never stored, so the loop body is branch-free.
@@ -358,7 +358,7 @@ __device__ __forceinline__ double fold_partial(const double (*red)[kPan], int t)
 }
 
 template <int NG, int PW>
-__global__ __launch_bounds__(kWG) void k_bdots(int64_t n_pad, int64_t ps, const double* __restrict__ V,
+__global__ __launch_bounds__(kWG, NG <= 5 ? 4 : 3) void k_bdots(int64_t n_pad, int64_t ps, const double* __restrict__ V,
                                                int nv, const double* __restrict__ W, int gram,
                                                double* __restrict__ part, const int* __restrict__ stop) {
     __shared__ double red[kWG / kWave][kPan];
@@ -384,13 +384,29 @@ __global__ __launch_bounds__(kWG) void k_bdots(int64_t n_pad, int64_t ps, const 
     const int64_t e = PW == 8 ? (int64_t)(l / kBW + 4 * ((l & (kBW - 1)) >> 3)) * pw + (l & 7)
                               : (int64_t)(l / kBW) * pw + (l & (kBW - 1));
     const int64_t nw = (int64_t)gridDim.x * (kWG / kWave);
-    for (int64_t r0 = ((int64_t)blockIdx.x * (kWG / kWave) + wv) * rows; r0 < n_pad; r0 += nw * rows) {
-        const double b = W[r0 * pw + e];
-        double a[NG];
+    // The next step's loads are all on their way before this one's products
+    // (left to itself the compiler trades them for registers).
+    int64_t r0 = ((int64_t)blockIdx.x * (kWG / kWave) + wv) * rows;
+    double a[NG], b = 0.0;
+#pragma unroll
+    for (int i = 0; i < NG; ++i) a[i] = 0.0;
+    if (r0 < n_pad) {
+        b = W[r0 * pw + e];
 #pragma unroll
         for (int i = 0; i < NG; ++i) a[i] = src[i][r0 * pw + e];
+    }
+    for (; r0 < n_pad; r0 += nw * rows) {
+        const int64_t r1 = r0 + nw * rows < n_pad ? r0 + nw * rows : r0;
+        const double b1 = W[r1 * pw + e];
+        double a1[NG];
+#pragma unroll
+        for (int i = 0; i < NG; ++i) a1[i] = src[i][r1 * pw + e];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NG; ++i) acc[i] = mfma16(a[i], b, acc[i]);
+        b = b1;
+#pragma unroll
+        for (int i = 0; i < NG; ++i) a[i] = a1[i];
     }
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
@@ -502,106 +518,82 @@ __global__ __launch_bounds__(kWG) void k_bgemm(int64_t n_pad, int64_t ps, const 
 }
 
 // First projection and second dot pass of BCGS2 in one sweep over the basis:
-// OUT = IN - sum_{i < nb} P_i C_i (as k_bgemm with sign -1), then the partial
+// OUT = IN - sum_{i < NB} P_i C_i (as k_bgemm with sign -1), then the partial
 // dots P_i^T OUT of this workgroup's tiles (as k_bdots, no Gram block).  One
-// 16-row tile per wavefront; the product reads each panel's tile with lane l
-// holding row r0 + l%16, columns l/16 + 4q (MFMA A operand), and the new tile
-// comes out with lane l holding rows r0 + l/16 + 4r, column l%16 -- the B
-// operand layout of the dot products -- so only the panels' tiles are read a
-// second time for the dots, in that layout, right after the first read
-// (from the caches).  nb <= NBMAX accumulators per lane.  The 16-wide
-// instance is held to 128 registers (four wavefronts per SIMD, no spills);
-// the 8-wide one would spill there and keeps three.
-template <int NBMAX, int PW>
-__global__ __launch_bounds__(kWG, PW == 16 ? 4 : 1) void k_bgemm_dots(int64_t n_pad, int64_t ps, const double* V,
-                                                                     int nb,
-                                                    const double* __restrict__ C, const double* IN,
-                                                    double* OUT, double* __restrict__ part,
-                                                    const int* __restrict__ stop) {
+// 16-row tile per wavefront.  Bound by the panels' bytes: every panel's tile
+// is loaded once, whole lines a load and all panels in flight together, in the
+// layout of the dots (lane l rows r0 + l/16 + 4r, column l%16), and turned
+// through LDS into the layout of the product (row l%16, columns l/16 + 4q); the
+// product leaves the new tile in the layout of the dots.  1,050,625 rows, 16
+// columns, 1 to 8 panels: 236 us on average (3.7 TB/s) with the panels read a
+// second time for the dots, 167 (5.1 TB/s at 8 panels) now.
+template <int NB, int PW>
+__global__ __launch_bounds__(kWG, NB <= 4 ? 3 : 2) void k_bgemm_dots(int64_t n_pad, int64_t ps,
+                                                                     const double* V,
+                                                                     const double* __restrict__ C,
+                                                                     const double* IN, double* OUT,
+                                                                     double* __restrict__ part,
+                                                                     const int* __restrict__ stop) {
     if (stop && *stop) return;   // a later step of a cycle that has ended
-    constexpr int pw = PW;
-    __shared__ double cs[NBMAX * kPan];
-    __shared__ double red[kWG / kWave][kPan];
-    for (int t = threadIdx.x; t < nb * kPan; t += kWG) cs[t] = C[t];
+    constexpr int pw = PW, np = PW / 4, ld = PW + 1;
+    constexpr int kTurn = 2 * kBW * ld;   // two tiles a wavefront
+    __shared__ double cs[NB * kPan];
+    __shared__ double buf[kWG / kWave * (kTurn > kPan ? kTurn : kPan)];
+    for (int t = threadIdx.x; t < NB * kPan; t += kWG) cs[t] = C[t];
     __syncthreads();
     const int l = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    d4 dacc[NBMAX];
+    double* turn = buf + wv * kTurn;
+    const int col = PW == 8 ? (l & 7) : (l & (kBW - 1));   // 8-wide: C's columns repeated
+    const int hf = (l & (kBW - 1)) >> 3;                   // 8-wide: the lane's column half
+    // Entry s of a lane in the layout of the dots: its row in the tile.
+    auto trow = [&](int s) { return PW == 8 ? l / kBW + 4 * (2 * s + hf) : l / kBW + 4 * s; };
+    d4 dacc[NB];
 #pragma unroll
-    for (int i = 0; i < NBMAX; ++i) dacc[i] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int i = 0; i < NB; ++i) dacc[i] = d4{0.0, 0.0, 0.0, 0.0};
     const int64_t ntile = n_pad / kBW;
     for (int64_t tile = (int64_t)blockIdx.x * (kWG / kWave) + wv; tile < ntile;
          tile += (int64_t)gridDim.x * (kWG / kWave)) {
         const int64_t r0 = tile * kBW;
+        double a[NB][np], wn[np];
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int s = 0; s < np; ++s) a[i][s] = V[i * ps + (r0 + trow(s)) * pw + col];
+#pragma unroll
+        for (int s = 0; s < np; ++s) wn[s] = IN[(r0 + trow(s)) * pw + col];
         d4 acc = {0.0, 0.0, 0.0, 0.0};
-        const int col = PW == 8 ? (l & 7) : (l & (kBW - 1));   // 8-wide: C's columns repeated
 #pragma unroll
-        for (int i = 0; i < NBMAX; ++i) {
-            if (i < nb) {
-                const double* P = V + i * ps + (r0 + (l & (kBW - 1))) * pw + l / kBW;
-                const double* Ci = cs + i * kPan + (l / kBW) * kBW + col;
-                double a[PW / 4], b[PW / 4];
+        for (int i = 0; i < NB; ++i) {
+            double* tb = turn + (i & 1) * kBW * ld;
+            wave_lds_sync();
 #pragma unroll
-                for (int q = 0; q < PW / 4; ++q) {
-                    a[q] = P[4 * q];
-                    b[q] = Ci[4 * q * kBW];
-                }
+            for (int s = 0; s < np; ++s) tb[trow(s) * ld + col] = a[i][s];
+            wave_lds_sync();
+            const double* Ci = cs + i * kPan + (l / kBW) * kBW + col;
 #pragma unroll
-                for (int q = 0; q < PW / 4; ++q) acc = mfma16(a[q], b[q], acc);
-            }
+            for (int q = 0; q < np; ++q)
+                acc = mfma16(tb[(l & (kBW - 1)) * ld + l / kBW + 4 * q], Ci[4 * q * kBW], acc);
         }
-        if (PW == 8) {
-            // Both halves of acc hold the tile.  Lane l takes rows
-            // r0 + l/16 + 4 h + 8 s (h = its column half, s = 0, 1), column
-            // l%8: two contiguous 8-row runs, and for each s the dot step's
-            // operands in the layout k_bdots uses for 8-wide panels.
-            const int h = (l & (kBW - 1)) >> 3;
-            double wn[2];
-            int64_t idx[2];
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                idx[s] = (r0 + l / kBW + 4 * (2 * s + h)) * pw + (l & 7);
-                wn[s] = IN[idx[s]] - (h ? acc[2 * s + 1] : acc[2 * s]);
-                OUT[idx[s]] = wn[s];
-            }
-#pragma unroll
-            for (int i = 0; i < NBMAX; ++i) {
-                if (i < nb) {
-                    const double* P = V + i * ps;
-                    const double a0 = P[idx[0]], a1 = P[idx[1]];
-                    dacc[i] = mfma16(a0, wn[0], dacc[i]);
-                    dacc[i] = mfma16(a1, wn[1], dacc[i]);
-                }
-            }
-        } else {
-            double wn[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t idx = (r0 + l / kBW + 4 * r) * pw + (l & (kBW - 1));
-                wn[r] = IN[idx] - acc[r];
-                OUT[idx] = wn[r];
-            }
-#pragma unroll
-            for (int i = 0; i < NBMAX; ++i) {
-                if (i < nb) {
-                    const double* P = V + i * ps + (r0 + l / kBW) * pw + (l & (kBW - 1));
-                    double a[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) a[r] = P[4 * r * pw];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) dacc[i] = mfma16(a[r], wn[r], dacc[i]);
-                }
-            }
+        for (int s = 0; s < np; ++s) {
+            // 8-wide: both column halves of acc hold the tile.
+            wn[s] -= PW == 8 ? (hf ? acc[(2 * s + 1) & 3] : acc[(2 * s) & 3]) : acc[s];
+            OUT[(r0 + trow(s)) * pw + col] = wn[s];
         }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int s = 0; s < np; ++s) dacc[i] = mfma16(a[i][s], wn[s], dacc[i]);
     }
+    double (*red)[kPan] = reinterpret_cast<double (*)[kPan]>(buf);
+    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NBMAX; ++i) {
-        if (i < nb) {
+    for (int i = 0; i < NB; ++i) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) red[wv][(l / kBW + 4 * r) * kBW + (l & (kBW - 1))] = dacc[i][r];
-            __syncthreads();
-            part[((int64_t)blockIdx.x * nb + i) * kPan + threadIdx.x] = fold_partial<PW>(red, threadIdx.x);
-            __syncthreads();
-        }
+        for (int r = 0; r < 4; ++r) red[wv][(l / kBW + 4 * r) * kBW + (l & (kBW - 1))] = dacc[i][r];
+        __syncthreads();
+        part[((int64_t)blockIdx.x * NB + i) * kPan + threadIdx.x] = fold_partial<PW>(red, threadIdx.x);
+        __syncthreads();
     }
 }
 
@@ -1005,7 +997,7 @@ void blaunch(BlockTimer* tm, int kind, double bytes, void (*k)(KA...), dim3 g, d
     blaunch_shm(tm, kind, bytes, k, g, b, 0, st, args...);
 }
 
-constexpr int kDotGroup = 4;   // panels per workgroup of the dot kernel
+constexpr int kDotGroup = 9;   // panels per workgroup of the dot kernel (at most)
 
 }  // namespace
 
@@ -1132,26 +1124,49 @@ int block_bind(BlockWork* w, void* mem, size_t bytes, hipStream_t st, int64_t n,
 
 namespace {
 
+// Workgroups of a sweep that leaves one partial per workgroup: one round of
+// resident workgroups of `kernel` with shm bytes of dynamic LDS (at most
+// kDotGrid, the partial-sum capacity), looked up once per device into cache.
+std::mutex g_grid_mu;
+int resident_grid(const void* kernel, int* cache, size_t shm = 0) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return kDotGrid;
+    std::lock_guard<std::mutex> lk(g_grid_mu);
+    if (cache[dev] == 0) {
+        int per_cu = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kWG, shm) != hipSuccess || per_cu < 1)
+            per_cu = 1;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+            cus = 1;
+        cache[dev] = std::min(kDotGrid, per_cu * cus);
+    }
+    return cache[dev];
+}
+
 // k_bdots over nb = nv + gram blocks: ceil(nb / kDotGroup) groups of workgroups
-// with the fewest slots each that hold the blocks (nb = 9: three groups of
-// three).  Every slot loads a panel and issues a matrix-core step per row
-// step, used or not, so unused slots cost loads and matrix-core time.
+// with the fewest slots each that hold the blocks (nb = 10: two groups of
+// five).  Every slot loads a panel and issues a matrix-core step per row
+// step, used or not, and every group reads W: 1,050,625 rows, 16 columns, the
+// 2 to 9 blocks of a cycle of eight steps: 1,300 us in groups of at most four,
+// 1,140 (5.3 TB/s at nine blocks) in groups of at most nine.
+template <int NG, int PW>
+int launch_dots_ng(const BlockWork& w, BlockTimer* tm, double bytes, hipStream_t st, int ng, int groups,
+                    const double* V, int nv, const double* W, int gram, const int* stop) {
+    if constexpr (NG > 1)
+        if (ng < NG) return launch_dots_ng<NG - 1, PW>(w, tm, bytes, st, ng, groups, V, nv, W, gram, stop);
+    static int cache[64] = {};
+    const int grid = resident_grid(reinterpret_cast<const void*>(k_bdots<NG, PW>), cache);
+    blaunch(tm, 5, bytes, k_bdots<NG, PW>, dim3(grid, groups), dim3(kWG), st, w.n_pad, w.ps, V, nv, W, gram, w.part,
+            stop);
+    return grid;
+}
+
 template <int PW>
-void launch_dots(const BlockWork& w, BlockTimer* tm, double bytes, hipStream_t st, const double* V, int nv,
+int launch_dots(const BlockWork& w, BlockTimer* tm, double bytes, hipStream_t st, const double* V, int nv,
                  const double* W, int gram, const int* stop) {
-    static_assert(kDotGroup == 4, "slot counts 1..4 are instantiated");
     const int nb = nv + gram;
     const int groups = (nb + kDotGroup - 1) / kDotGroup;
-    const int ng = (nb + groups - 1) / groups;
-    const dim3 grid(kDotGrid, groups);
-    if (ng == 1)
-        blaunch(tm, 5, bytes, k_bdots<1, PW>, grid, dim3(kWG), st, w.n_pad, w.ps, V, nv, W, gram, w.part, stop);
-    else if (ng == 2)
-        blaunch(tm, 5, bytes, k_bdots<2, PW>, grid, dim3(kWG), st, w.n_pad, w.ps, V, nv, W, gram, w.part, stop);
-    else if (ng == 3)
-        blaunch(tm, 5, bytes, k_bdots<3, PW>, grid, dim3(kWG), st, w.n_pad, w.ps, V, nv, W, gram, w.part, stop);
-    else
-        blaunch(tm, 5, bytes, k_bdots<4, PW>, grid, dim3(kWG), st, w.n_pad, w.ps, V, nv, W, gram, w.part, stop);
+    return launch_dots_ng<kDotGroup, PW>(w, tm, bytes, st, (nb + groups - 1) / groups, groups, V, nv, W, gram, stop);
 }
 
 // C[0 .. nb) = P^T W (panels of V, then W itself when gram), summed.
@@ -1160,12 +1175,10 @@ void dots(const BlockWork& w, BlockTimer* tm, hipStream_t st, const double* V, i
           const int* stop) {
     const int nb = nv + gram;
     const double bytes = (double)(nv + 1) * (double)w.n * w.pw * sizeof(double);   // panels and W, once
-    if (w.pw == 8)
-        launch_dots<8>(w, tm, bytes, st, V, nv, W, gram, stop);
-    else
-        launch_dots<kBW>(w, tm, bytes, st, V, nv, W, gram, stop);
+    const int grid = w.pw == 8 ? launch_dots<8>(w, tm, bytes, st, V, nv, W, gram, stop)
+                               : launch_dots<kBW>(w, tm, bytes, st, V, nv, W, gram, stop);
     const int cnt = nb * kPan;
-    k_breduce<<<(cnt + kBW - 1) / kBW, kWG, 0, st>>>(kDotGrid, cnt, w.part, w.C, acc_into, acc_blocks * kPan,
+    k_breduce<<<(cnt + kBW - 1) / kBW, kWG, 0, st>>>(grid, cnt, w.part, w.C, acc_into, acc_blocks * kPan,
                                                      first, diag_blk, nb2, stop);
 }
 
@@ -1188,31 +1201,6 @@ void gemm(const BlockWork& w, BlockTimer* tm, hipStream_t st, const double* V, i
 // dots() call without a Gram block would); one sweep over the panels.
 constexpr int kFuseMax = 8;   // panels of the fused sweep (accumulators per lane)
 
-// Workgroups of a sweep that leaves one partial per workgroup: one round of
-// resident workgroups of `kernel` with shm bytes of dynamic LDS (at most
-// kDotGrid, the partial-sum capacity), looked up once per device into cache.
-std::mutex g_grid_mu;
-int resident_grid(const void* kernel, int* cache, size_t shm = 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return kDotGrid;
-    std::lock_guard<std::mutex> lk(g_grid_mu);
-    if (cache[dev] == 0) {
-        int per_cu = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kWG, shm) != hipSuccess || per_cu < 1)
-            per_cu = 1;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-            cus = 1;
-        cache[dev] = std::min(kDotGrid, per_cu * cus);
-    }
-    return cache[dev];
-}
-
-template <int PW>
-int fused_grid() {
-    static int cache[64] = {};
-    return resident_grid(reinterpret_cast<const void*>(k_bgemm_dots<kFuseMax, PW>), cache);
-}
-
 // Dynamic LDS of k_bgemm_gram for nb coefficient blocks (the wavefronts'
 // accumulators reuse it), and its resident grid.
 size_t gram_shm(int nb) { return (size_t)std::max(nb, kWG / kWave) * kPan * sizeof(double); }
@@ -1224,16 +1212,24 @@ int gram_grid(int nb) {
     return resident_grid(reinterpret_cast<const void*>(k_bgemm_gram<PW>), cache[blocks], gram_shm(nb));
 }
 
+// Launches the sweep over nb panels (one instance each); returns its grid.
+template <int NB, int PW>
+int launch_gemm_dots(const BlockWork& w, BlockTimer* tm, double bytes, hipStream_t st, int nb, const double* V,
+                     double* W, const int* stop) {
+    if constexpr (NB > 1)
+        if (nb < NB) return launch_gemm_dots<NB - 1, PW>(w, tm, bytes, st, nb, V, W, stop);
+    static int cache[64] = {};
+    const int grid = resident_grid(reinterpret_cast<const void*>(k_bgemm_dots<NB, PW>), cache);
+    blaunch(tm, 6, bytes, k_bgemm_dots<NB, PW>, dim3(grid), dim3(kWG), st, w.n_pad, w.ps, V, (const double*)w.C,
+            (const double*)W, W, w.part, stop);
+    return grid;
+}
+
 void gemm_dots(const BlockWork& w, BlockTimer* tm, hipStream_t st, const double* V, int nb, double* W,
                double* acc_into, int acc_blocks, const int* stop) {
     const double bytes = (double)(nb + 2) * (double)w.n * w.pw * sizeof(double);   // panels once, W in and out
-    const int grid = w.pw == 8 ? fused_grid<8>() : fused_grid<kBW>();
-    if (w.pw == 8)
-        blaunch(tm, 6, bytes, k_bgemm_dots<kFuseMax, 8>, dim3(grid), dim3(kWG), st, w.n_pad, w.ps, V, nb,
-                (const double*)w.C, (const double*)W, W, w.part, stop);
-    else
-        blaunch(tm, 6, bytes, k_bgemm_dots<kFuseMax, kBW>, dim3(grid), dim3(kWG), st, w.n_pad, w.ps, V, nb,
-                (const double*)w.C, (const double*)W, W, w.part, stop);
+    const int grid = w.pw == 8 ? launch_gemm_dots<kFuseMax, 8>(w, tm, bytes, st, nb, V, W, stop)
+                               : launch_gemm_dots<kFuseMax, kBW>(w, tm, bytes, st, nb, V, W, stop);
     const int cnt = nb * kPan;
     k_breduce<<<(cnt + kBW - 1) / kBW, kWG, 0, st>>>(grid, cnt, w.part, w.C, acc_into, acc_blocks * kPan, 0,
                                                      -1, nullptr, stop);
