@@ -131,6 +131,7 @@ struct gmres_plan_s {
     float* azv32 = nullptr;
     int64_t az_nnz = 0;
     double *E = nullptr, *Einv = nullptr;
+    int* lu_piv = nullptr;  // row exchanges of E's factors
     // sliced ELL copies (forward op / adjoint op)
     int *sell_off = nullptr, *sell_src = nullptr;
     int *sell_perm = nullptr, *tsell_perm = nullptr;   // sorted row order (NULL: unsorted)
@@ -267,7 +268,7 @@ gmres_status refresh_values(gmres_plan_s* p) {
     if (p->R > 0) {
         az_fill(sa, p->rowptr, p->colind, p->vals, p->azrp, p->azci, p->azv);
         build_coarse(sa, p->ztrp, p->ztci, p->ztv, p->azrp, p->azci, p->azv, p->d_e_off, p->E);
-        CHECK(to_status(lu_inverse(p->st, p->nsys, p->d_zcol_off, p->d_e_off, p->E, p->Einv,
+        CHECK(to_status(lu_inverse(p->st, p->nsys, p->R, p->d_zcol_off, p->d_e_off, p->E, p->lu_piv, p->Einv,
                                    p->d_flags), "coarse LU"));
         if (p->azv32) to_f32(p->st, p->az_nnz, p->azv, p->azv32);
     }
@@ -459,6 +460,7 @@ void carve_phase1(gmres_plan_s* p, Arena& A) {
         p->azrp = A.take_n<int>(n + 1);
         p->E = A.take_n<double>(p->e_off_h[nsys]);
         p->Einv = A.take_n<double>(p->e_off_h[nsys]);
+        p->lu_piv = A.take_n<int>(p->R);
         // Z^T chunk partials: at most ceil(longest Z^T row / CH) per column.
         p->mc_cap = std::max<int64_t>(1, (std::min<int64_t>(n, zn) + p->CH - 1) / p->CH);
         if (nsys == 1) {

@@ -249,8 +249,8 @@ void az_fill(const SetupArgs& a, const int* rowptr, const int* colind, const dou
 void build_coarse(const SetupArgs& a, const int* ztrp, const int* ztci, const double* ztv,
                   const int* azrp, const int* azci, const double* azv, const int64_t* d_e_off,
                   double* E);
-int lu_inverse(hipStream_t st, int nsys, const int64_t* d_sys_zcol_off, const int64_t* d_e_off,
-               double* E, double* Einv, int* d_flags);
+int lu_inverse(hipStream_t st, int nsys, int ncols, const int64_t* d_sys_zcol_off, const int64_t* d_e_off,
+               double* E, int* piv, double* Einv, int* d_flags);
 void to_f32(hipStream_t st, int64_t n, const double* src, float* dst);
 void grad_vals(hipStream_t st, int64_t n, const int* rowptr, const int* colind, const double* lam,
                const double* x, double* g);

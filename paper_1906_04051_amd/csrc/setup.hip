@@ -481,14 +481,18 @@ void az_fill(const SetupArgs& a, const int* rowptr, const int* colind, const dou
 }
 
 // ------------------------------------------------------- coarse matrix E
-// One thread per entry E_s[a][k] = sum_{i in Z^T row a} z_ia (A Z)_{i,k}
-// (row-major per system, offsets e_off).
-__global__ void k_build_e(int nsys, const int64_t* __restrict__ zcol_off,
+// One wavefront per entry E_s[a][k] = sum_{i in Z^T row a} z_ia (A Z)_{i,k}
+// (row-major per system, offsets e_off), its lanes sharing the rows of column a
+// (fixed order).  Bound by the latency of row -> A Z entries: 40,401 rows, 64
+// columns: 311 us with a thread per entry (64 wavefronts in all), 18 us;
+// 1,050,625 rows: 7.7 ms, 0.34 now.
+__global__ __launch_bounds__(kWG) void k_build_e(int nsys, const int64_t* __restrict__ zcol_off,
                           const int64_t* __restrict__ e_off, const int* __restrict__ ztrp,
                           const int* __restrict__ ztci, const double* __restrict__ ztv,
                           const int* __restrict__ azrp, const int* __restrict__ azci,
                           const double* __restrict__ azv, double* __restrict__ E) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t p = (int64_t)blockIdx.x * (kWG / kWave) + threadIdx.x / kWave;
+    const int ln = threadIdx.x & (kWave - 1);
     if (p >= e_off[nsys]) return;
     const int s = sys_of_row(e_off, nsys, p);
     const int64_t c0 = zcol_off[s];
@@ -497,12 +501,15 @@ __global__ void k_build_e(int nsys, const int64_t* __restrict__ zcol_off,
     const int a = (int)(loc / r), k = (int)(loc % r);
     const int col = (int)(c0 + k);
     double acc = 0.0;
-    for (int q = ztrp[c0 + a]; q < ztrp[c0 + a + 1]; ++q) {
+    const int q1 = ztrp[c0 + a + 1];
+#pragma unroll 4
+    for (int q = ztrp[c0 + a] + ln; q < q1; q += kWave) {
         const int i = ztci[q];
         for (int t = azrp[i]; t < azrp[i + 1]; ++t)
             if (azci[t] == col) acc += ztv[q] * azv[t];
     }
-    E[p] = acc;
+    acc = gwave_sum(acc);
+    if (ln == 0) E[p] = acc;
 }
 
 void build_coarse(const SetupArgs& a, const int* ztrp, const int* ztci, const double* ztv,
@@ -512,116 +519,168 @@ void build_coarse(const SetupArgs& a, const int* ztrp, const int* ztci, const do
     hipMemcpyAsync(&total, d_e_off + a.nsys, sizeof(int64_t), hipMemcpyDeviceToHost, a.st);
     hipStreamSynchronize(a.st);
     if (total > 0)
-        k_build_e<<<blocks_for(total), kWG, 0, a.st>>>(a.nsys, a.d_sys_zcol_off, d_e_off, ztrp, ztci,
+        k_build_e<<<blocks_for(total * kWave), kWG, 0, a.st>>>(a.nsys, a.d_sys_zcol_off, d_e_off, ztrp, ztci,
                                                       ztv, azrp, azci, azv, E);
 }
 
 // LU with partial pivoting of each E_s (row-major, in place; one workgroup per
-// system), then the explicit inverse column by column, stored column-major
-// (Einv_s[a*r + i] = (E_s^{-1})_{i,a}).  Pivot = first row of largest |.|;
-// singular when |pivot| <= r * eps * max|E_s| (flags bit 2).
-__global__ __launch_bounds__(kWG) void k_lu_inverse(const int64_t* __restrict__ zcol_off,
-                                                    const int64_t* __restrict__ e_off,
-                                                    double* __restrict__ Eall,
-                                                    double* __restrict__ Einv_all,
-                                                    int* __restrict__ flags) {
+// system).  Pivot = first row of largest |.|; singular when |pivot| <= r * eps *
+// max|E_s| (flags bit 2).  Matrices of up to kLuLds columns are factored in LDS:
+// every pivot is a chain of a reduction, an exchange, a division and an update,
+// and a pass over memory in each costs more than the arithmetic.  r = 64:
+// 600 us with the matrix in memory and the inverse's columns a thread each;
+// 99 us here and 31 us for the columns now.
+constexpr int kLuLds = 96;
+
+__global__ __launch_bounds__(kWG) void k_lu(const int64_t* __restrict__ zcol_off,
+                                            const int64_t* __restrict__ e_off, double* __restrict__ Eall,
+                                            int* __restrict__ piv_all, int* __restrict__ flags) {
     const int s = blockIdx.x;
     const int r = (int)(zcol_off[s + 1] - zcol_off[s]);
     if (r == 0) return;
-    double* E = Eall + e_off[s];
-    double* X = Einv_all + e_off[s];
-    __shared__ double rv[kWG];
-    __shared__ int ri[kWG];
-    __shared__ int piv[kMaxR];
-    __shared__ int sing;
+    double* Eg = Eall + e_off[s];
+    int* piv = piv_all + zcol_off[s];
+    __shared__ double El[kLuLds * (kLuLds + 1)];
+    __shared__ double rv[kWG / kWave];
+    __shared__ double pmax;
+    __shared__ int prow;
+    const bool in_lds = r <= kLuLds;
+    const int t = threadIdx.x, ln = t & (kWave - 1), wv = t / kWave;
+    const int ld = in_lds ? r | 1 : r;   // odd: rows and columns without conflicts
     // max |E|
     double mx = 0.0;
-    for (int64_t q = threadIdx.x; q < (int64_t)r * r; q += kWG) mx = fmax(mx, fabs(E[q]));
-    rv[threadIdx.x] = mx;
-    __syncthreads();
-    for (int o = kWG / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) rv[threadIdx.x] = fmax(rv[threadIdx.x], rv[threadIdx.x + o]);
-        __syncthreads();
+    for (int q = t; q < r * r; q += kWG) {
+        const double v = Eg[q];
+        mx = fmax(mx, fabs(v));
+        if (in_lds) El[q / r * ld + q % r] = v;
     }
-    const double tiny = (double)r * 2.220446049250313e-16 * rv[0];
-    if (threadIdx.x == 0) sing = 0;
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, kWave));
+    if (ln == 0) rv[wv] = mx;
     __syncthreads();
-    for (int k = 0; k < r; ++k) {
-        double best = -1.0;
-        int bi = r;
-        for (int i = k + threadIdx.x; i < r; i += kWG) {
-            const double v = fabs(E[(int64_t)i * r + k]);
-            if (v > best) { best = v; bi = i; }
-        }
-        rv[threadIdx.x] = best;
-        ri[threadIdx.x] = bi;
-        __syncthreads();
-        for (int o = kWG / 2; o > 0; o >>= 1) {
-            if (threadIdx.x < o) {
-                const double b2 = rv[threadIdx.x + o];
-                const int i2 = ri[threadIdx.x + o];
-                if (b2 > rv[threadIdx.x] || (b2 == rv[threadIdx.x] && i2 < ri[threadIdx.x])) {
-                    rv[threadIdx.x] = b2;
-                    ri[threadIdx.x] = i2;
+    for (int w = 0; w < kWG / kWave; ++w) mx = fmax(mx, rv[w]);
+    const double tiny = (double)r * 2.220446049250313e-16 * mx;
+    auto factor = [&](auto* E) {
+        for (int k = 0; k < r; ++k) {
+            if (wv == 0) {
+                double best = -1.0;
+                int bi = r;
+                for (int i = k + ln; i < r; i += kWave) {
+                    const double v = fabs(E[i * ld + k]);
+                    if (v > best) { best = v; bi = i; }
+                }
+#pragma unroll
+                for (int o = kWave / 2; o > 0; o >>= 1) {
+                    const double b2 = __shfl_xor(best, o, kWave);
+                    const int i2 = __shfl_xor(bi, o, kWave);
+                    if (b2 > best || (b2 == best && i2 < bi)) { best = b2; bi = i2; }
+                }
+                if (ln == 0) {
+                    pmax = best;
+                    prow = bi;
+                    piv[k] = bi;
                 }
             }
             __syncthreads();
-        }
-        const int p = ri[0];
-        if (threadIdx.x == 0) {
-            piv[k] = p;
-            if (!(rv[0] > tiny)) sing = 1;
-        }
-        __syncthreads();
-        if (sing) break;
-        if (p != k)
-            for (int j = threadIdx.x; j < r; j += kWG) {
-                const double t = E[(int64_t)k * r + j];
-                E[(int64_t)k * r + j] = E[(int64_t)p * r + j];
-                E[(int64_t)p * r + j] = t;
+            if (!(pmax > tiny)) return false;
+            const int p = prow;
+            if (p != k)
+                for (int j = t; j < r; j += kWG) {
+                    const double v = E[k * ld + j];
+                    E[k * ld + j] = E[p * ld + j];
+                    E[p * ld + j] = v;
+                }
+            __syncthreads();
+            const double pk = E[k * ld + k];
+            for (int i = k + 1 + t; i < r; i += kWG) E[i * ld + k] /= pk;
+            __syncthreads();
+            // Sixteen columns by sixteen rows a pass.
+            for (int i = k + 1 + t / 16; i < r; i += kWG / 16) {
+                const double l = E[i * ld + k];
+                for (int j = k + 1 + t % 16; j < r; j += 16) E[i * ld + j] -= l * E[k * ld + j];
             }
-        __syncthreads();
-        const double pk = E[(int64_t)k * r + k];
-        for (int i = k + 1 + threadIdx.x; i < r; i += kWG) E[(int64_t)i * r + k] /= pk;
-        __syncthreads();
-        const int64_t w = r - k - 1;
-        for (int64_t q = threadIdx.x; q < w * w; q += kWG) {
-            const int i = k + 1 + (int)(q / w), j = k + 1 + (int)(q % w);
-            E[(int64_t)i * r + j] -= E[(int64_t)i * r + k] * E[(int64_t)k * r + j];
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    if (sing) {
-        if (threadIdx.x == 0) atomicOr(flags, 4);
+        return true;
+    };
+    if (!in_lds) {
+        if (!factor(Eg) && t == 0) atomicOr(flags, 4);
         return;
     }
-    // Column a of the inverse: solve (P L U) x = e_a.
-    for (int a = threadIdx.x; a < r; a += kWG) {
-        double* x = X + (int64_t)a * r;
-        for (int i = 0; i < r; ++i) x[i] = (i == a) ? 1.0 : 0.0;
-        for (int k = 0; k < r; ++k)
-            if (piv[k] != k) {
-                const double t = x[k];
-                x[k] = x[piv[k]];
-                x[piv[k]] = t;
-            }
-        for (int i = 0; i < r; ++i) {
-            double v = x[i];
-            for (int j = 0; j < i; ++j) v -= E[(int64_t)i * r + j] * x[j];
-            x[i] = v;
-        }
-        for (int i = r - 1; i >= 0; --i) {
-            double v = x[i];
-            for (int j = i + 1; j < r; ++j) v -= E[(int64_t)i * r + j] * x[j];
-            x[i] = v / E[(int64_t)i * r + i];
-        }
+    if (!factor((__attribute__((address_space(3))) double*)El)) {
+        if (t == 0) atomicOr(flags, 4);
+        return;
     }
+    for (int q = t; q < r * r; q += kWG) Eg[q] = El[q / r * ld + q % r];
 }
 
-int lu_inverse(hipStream_t st, int nsys, const int64_t* d_sys_zcol_off, const int64_t* d_e_off,
-               double* E, double* Einv, int* d_flags) {
+// Column a of the inverse, (P L U) x = e_a, stored column-major (Einv_s[a*r + i]
+// = (E_s^{-1})_{i,a}): one wavefront, lane i holding entries i, i + 64, ...; a
+// substitution step is a lane broadcast and a multiply-add with a column of the
+// factors.
+__global__ __launch_bounds__(kWave) void k_lu_columns(const int64_t* __restrict__ zcol_off,
+                                                      const int64_t* __restrict__ e_off,
+                                                      const double* __restrict__ Eall,
+                                                      const int* __restrict__ piv_all,
+                                                      double* __restrict__ Einv_all,
+                                                      const int* __restrict__ flags, int nsys) {
+    if (*flags & 4) return;
+    const int64_t c = blockIdx.x;
+    const int s = sys_of_row(zcol_off, nsys, c);
+    const int r = (int)(zcol_off[s + 1] - zcol_off[s]), a = (int)(c - zcol_off[s]);
+    const double* E = Eall + e_off[s];
+    const int* piv = piv_all + zcol_off[s];
+    double* X = Einv_all + e_off[s] + (int64_t)a * r;
+    const int ln = threadIdx.x;
+    constexpr int NQ = kMaxR / kWave;
+    // The unit entry's place after the row exchanges.
+    int at = a;
+    for (int k = 0; k < r; ++k) {
+        const int p = piv[k];
+        at = at == k ? p : at == p ? k : at;
+    }
+    double x[NQ];
+    int row[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        x[q] = ln + q * kWave == at ? 1.0 : 0.0;
+        row[q] = min(ln + q * kWave, r - 1) * r;
+    }
+    const int nq = (r + kWave - 1) / kWave;
+#pragma unroll
+    for (int h = 0; h < NQ; ++h)
+#pragma unroll 4
+        for (int k = h * kWave; k < min(r, (h + 1) * kWave); ++k) {
+            const double xk = lane_value(x[h], k - h * kWave);
+#pragma unroll
+            for (int q = h; q < NQ; ++q)
+                if (q < nq) {
+                    const double l = E[row[q] + k];
+                    if (ln + q * kWave > k) x[q] -= l * xk;
+                }
+        }
+#pragma unroll
+    for (int h = NQ - 1; h >= 0; --h)
+#pragma unroll 4
+        for (int k = min(r, (h + 1) * kWave) - 1; k >= h * kWave; --k) {
+            const double xk = lane_value(x[h], k - h * kWave) / E[k * r + k];
+            if (ln == k - h * kWave) x[h] = xk;
+#pragma unroll
+            for (int q = 0; q <= h; ++q) {
+                const double u = E[row[q] + k];
+                if (ln + q * kWave < k) x[q] -= u * xk;
+            }
+        }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        if (ln + q * kWave < r) X[ln + q * kWave] = x[q];
+}
+
+int lu_inverse(hipStream_t st, int nsys, int ncols, const int64_t* d_sys_zcol_off, const int64_t* d_e_off,
+               double* E, int* piv, double* Einv, int* d_flags) {
     hipMemsetAsync(d_flags, 0, sizeof(int), st);
-    k_lu_inverse<<<nsys, kWG, 0, st>>>(d_sys_zcol_off, d_e_off, E, Einv, d_flags);
+    k_lu<<<nsys, kWG, 0, st>>>(d_sys_zcol_off, d_e_off, E, piv, d_flags);
+    k_lu_columns<<<ncols, kWave, 0, st>>>(d_sys_zcol_off, d_e_off, E, piv, Einv, d_flags, nsys);
     int h = 0;
     hipMemcpyAsync(&h, d_flags, sizeof(int), hipMemcpyDeviceToHost, st);
     if (hipStreamSynchronize(st) != hipSuccess) return kStatusDevice;
