@@ -310,6 +310,11 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
         int row[RPT];    // system-local row (0 where there is none)
         bool ok[RPT];
         bool wact = wv * kWave < RW;    // this wavefront holds rows
+        // Its row slots in use (RW is a multiple of the wavefront): with three
+        // or four slots a thread the basis loads of the others are skipped, and
+        // in the dots those of rows that do not exist (the same solve: 31.4 ms
+        // with a select per loaded entry instead, 26.7 so).
+        const int qn = uni((RW - wv * kWave + kGN - 1) / kGN);
 #pragma unroll
         for (int q = 0; q < RPT; ++q) {
             const int r = tid + q * kGN;
@@ -322,10 +327,14 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
         // it with coefficient 0.
         for (int i = tid; i < min(nl, m) * RW; i += kGN) Vl[i] = (ST)0;
         for (int i = tid; i < kGW * (kMP + 8 + kAU); i += kGN) red[0][i] = 0.0;
-        // Place in global overflow columns (every row slot has a valid one).
+        // Place in global overflow columns (every row slot has a valid one): the
+        // position, whose neighbours are the neighbouring lanes, unless the
+        // basis is read by rows afterwards (265,225 sorted Q2 rows, FP32 basis:
+        // 32.4 ms a mixed solve by rows, 31.4 by positions).
         int64_t gpos[RPT];
 #pragma unroll
-        for (int q = 0; q < RPT; ++q) gpos[q] = ok[q] ? row[q] : 0;
+        for (int q = 0; q < RPT; ++q)
+            gpos[q] = ADAPT ? (ok[q] ? row[q] : 0) : (ok[q] ? p0 + pos[q] : min(p0, n - 1));
 
         // Rows without A Z entries multiply s_0 by zero, listed or not.
         for (int i = tid; i < kMaxR; i += kGN) sv[i] = 0.0;
@@ -705,8 +714,10 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
         };
         // Eight consecutive basis columns c .. c+7 of row slot q (columns
         // past nv - 1 repeat it).  A chunk is in LDS or in global memory as a
-        // whole: nl is a multiple of eight or covers every column.
-        auto vload = [&](int c, int nv, int q, ACC (&v)[8]) {
+        // whole: nl is a multiple of eight or covers every column.  A row that
+        // does not exist reads its neighbour's entry, which may not have been
+        // written yet: zero with drop, else for the caller to discard.
+        auto vload = [&](int c, int nv, int q, ACC (&v)[8], bool drop = false) {
             if (c < nl) {
                 const GM_LDS ST* bp = Vl + pos[q];
 #pragma unroll
@@ -715,10 +726,8 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                 const GM_GLB ST* bp = (const GM_GLB ST*)(Vg + gpos[q]);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    // A row that does not exist reads its neighbour's entry,
-                    // which may not have been written yet: dropped.
                     const ACC t = (ACC)bp[min(c + e, nv - 1) * ldv];
-                    v[e] = ok[q] ? t : (ACC)0;
+                    v[e] = !drop || ok[q] ? t : (ACC)0;
                 }
             }
         };
@@ -773,9 +782,10 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                     for (int e = 0; e < 16; ++e) acc[e] = 0;
 #pragma unroll
                     for (int q = 0; q < RPT; ++q) {
+                        if (RPT > 2 && !ok[q]) continue;
                         ACC v[8], v2[8];
-                        vload(c, nv, q, v);
-                        vload(c + 8, nv, q, v2);
+                        vload(c, nv, q, v, RPT <= 2);
+                        vload(c + 8, nv, q, v2, RPT <= 2);
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
                             acc[e] += v[e] * u[q];
@@ -792,8 +802,9 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                     for (int e = 0; e < 8; ++e) acc[e] = 0;
 #pragma unroll
                     for (int q = 0; q < RPT; ++q) {
+                        if (RPT > 2 && !ok[q]) continue;
                         ACC v[8];
-                        vload(c, nv, q, v);
+                        vload(c, nv, q, v, RPT <= 2);
 #pragma unroll
                         for (int e = 0; e < 8; ++e) acc[e] += v[e] * u[q];
                     }
@@ -1054,6 +1065,7 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                             }
 #pragma unroll
                             for (int q = 0; q < RPT; ++q) {
+                                if (RPT > 2 && q >= qn) continue;
                                 ACC v[8];
                                 vload(c, j, q, v);
 #pragma unroll
@@ -1098,6 +1110,7 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                             for (int e = 0; e < 8; ++e) k1[e] = c1[c + e];
 #pragma unroll
                             for (int q = 0; q < RPT; ++q) {
+                                if (RPT > 2 && q >= qn) continue;
                                 ACC v[8];
                                 vload(c, j + 1, q, v);
 #pragma unroll
