@@ -82,7 +82,8 @@ typedef struct {
                                  (project, re-project, update); 1 = CGS2 in two sweeps with lagged
                                  normalisation (the SpMV of step j+1 runs on the once-projected
                                  vector; the second update is folded into the next sweep through
-                                 the Arnoldi relation); 2 = CGS2 with one reduction per step
+                                 the Arnoldi relation), two steps per pair of sweeps where nothing
+                                 else is needed between them; 2 = CGS2 with one reduction per step
                                  (delayed re-orthogonalisation: one dot sweep of q and A q against
                                  the basis, one update sweep; FP64 single-system plans without
                                  adaptive deflation).  Equal in exact arithmetic. */
