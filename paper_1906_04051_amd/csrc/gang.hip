@@ -578,7 +578,9 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                 }
             }
         };
-        // Z^T u partials of the own rows: tpart (K > 1) or tv.
+        // Z^T u partials of the own rows: tpart (K > 1) or tv.  Its last reads
+        // of zred are not followed by a barrier: one has to come before coarse,
+        // whose waves write zred whenever the sums they wait for are there.
         auto zt_out = [&](const ACC (&u)[RPT]) {
             for (int z0 = 0; z0 < nz; z0 += kZS) {
                 const int ze = min(nz, z0 + kZS);
@@ -921,6 +923,8 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                     done = 1;
                 }
                 init = false;
+            } else {
+                __syncthreads();   // zt_out, then coarse
             }
             if (R > 0) {
                 coarse();
