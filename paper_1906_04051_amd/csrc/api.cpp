@@ -1051,7 +1051,8 @@ struct GangShape {
 
 GangShape gang_shape(const gmres_plan_s* p, int op, int prec) {
     GangShape g;
-    const bool sell = op ? p->tsell_col != nullptr : p->sell_col != nullptr;
+    // A copy without a single entry has nothing the kernel's idle lanes could read.
+    const bool sell = op ? p->tsell_col && p->tsell_total > 0 : p->sell_col && p->sell_total > 0;
     if (p->nsys != 1 || p->o.ortho != 1 || p->timer.period > 0 || !sell ||
         (p->o.spmv_lanes != 0 && p->o.spmv_lanes != kSell) || p->o.num_blocks > 0)
         return g;
@@ -1894,7 +1895,7 @@ static gmres_status plan_batch_gangs(gmres_plan_s* p) {
     int cus = 0, lds_max = 0;
     HIP_OK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
     HIP_OK(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, p->device));
-    if (!p->sell_col || p->sell_perm || p->o.batch_wg > 0 || p->o.batch_lanes > 0) return GMRES_OK;
+    if (!p->sell_col || p->sell_total == 0 || p->sell_perm || p->o.batch_wg > 0 || p->o.batch_lanes > 0) return GMRES_OK;
     static const int kSize[kGangCls] = {256, 192, 128, 96, 64, 48, 32, 24, 16, 12, 8, 6, 4, 3, 2, 1};
     const int wgs = std::min(cus, kGangWG);
     auto rows = [&](int s) { return p->row_off[s + 1] - p->row_off[s]; };

@@ -496,6 +496,7 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                 const int o0 = h.sell_off[sl];
                 off = o0 + (gp & 63);
                 wid = (h.sell_off[sl + 1] - o0) / kWave;
+                if (wid == 0) off = 0;   // a slice of empty rows has no entry of its own
             }
         };
         auto mload = [&]() {
@@ -503,20 +504,21 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
 #pragma unroll
                 for (int q = 0; q < RPT; ++q) {
                     int64_t off = 0;
-                    int wid = 1;
+                    int wid = 0;
                     if (ok[q]) slice_of(q, off, wid);
-                    // Branch-free: entries past the width repeat the last one
-                    // with value 0 (rows that do not exist read entry 0).
+                    // Branch-free: loads past the width repeat the last entry
+                    // (entry 0 for rows that do not exist and slices without
+                    // entries), and stand for 0 times the row's own element.
 #pragma unroll
                     for (int k = 0; k < WF; ++k) {
-                        const int64_t e = off + (int64_t)min(k, wid - 1) * kWave;
+                        const int64_t e = off + (int64_t)max(min(k, wid - 1), 0) * kWave;
                         mc[q][k] = (int)h.sell_col[e];
                         mv[q][k] = ((const AT*)h.sell_val)[e];
                     }
 #pragma unroll
                     for (int k = 0; k < WF; ++k) {
-                        mc[q][k] = ok[q] ? mc[q][k] : 0;
-                        mv[q][k] = ok[q] && k < wid ? mv[q][k] : (AT)0;
+                        mc[q][k] = k < wid ? mc[q][k] : 0;
+                        mv[q][k] = k < wid ? mv[q][k] : (AT)0;
                     }
                 }
             }
@@ -545,13 +547,13 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
 #pragma unroll
                 for (int q = 0; q < RPT; ++q) {
                     int64_t off = 0;
-                    int wid = 1;
+                    int wid = 0;
                     if (ok[q]) slice_of(q, off, wid);
                     int cc[CH];
                     AT vv[CH];
 #pragma unroll
                     for (int k = 0; k < CH; ++k) {
-                        const int64_t e = off + (int64_t)min(k, wid - 1) * kWave;
+                        const int64_t e = off + (int64_t)max(min(k, wid - 1), 0) * kWave;
                         cc[k] = h.sell_col[e];
                         vv[k] = ((const AT*)h.sell_val)[e];
                     }
