@@ -485,31 +485,35 @@ void az_fill(const SetupArgs& a, const int* rowptr, const int* colind, const dou
 // (row-major per system, offsets e_off), its lanes sharing the rows of column a
 // (fixed order).  Bound by the latency of row -> A Z entries: 40,401 rows, 64
 // columns: 311 us with a thread per entry (64 wavefronts in all), 18 us;
-// 1,050,625 rows: 7.7 ms, 0.34 now.
+// 1,050,625 rows: 7.7 ms, 0.34 now.  Past kEGrid workgroups a wavefront takes
+// several entries (a launch holds fewer than 2^32 threads: 2^26 entries).
+constexpr int64_t kEGrid = int64_t(1) << 20;
+
 __global__ __launch_bounds__(kWG) void k_build_e(int nsys, const int64_t* __restrict__ zcol_off,
                           const int64_t* __restrict__ e_off, const int* __restrict__ ztrp,
                           const int* __restrict__ ztci, const double* __restrict__ ztv,
                           const int* __restrict__ azrp, const int* __restrict__ azci,
                           const double* __restrict__ azv, double* __restrict__ E) {
-    const int64_t p = (int64_t)blockIdx.x * (kWG / kWave) + threadIdx.x / kWave;
     const int ln = threadIdx.x & (kWave - 1);
-    if (p >= e_off[nsys]) return;
-    const int s = sys_of_row(e_off, nsys, p);
-    const int64_t c0 = zcol_off[s];
-    const int r = (int)(zcol_off[s + 1] - c0);
-    const int64_t loc = p - e_off[s];
-    const int a = (int)(loc / r), k = (int)(loc % r);
-    const int col = (int)(c0 + k);
-    double acc = 0.0;
-    const int q1 = ztrp[c0 + a + 1];
+    const int64_t total = e_off[nsys], stride = (int64_t)gridDim.x * (kWG / kWave);
+    for (int64_t p = (int64_t)blockIdx.x * (kWG / kWave) + threadIdx.x / kWave; p < total; p += stride) {
+        const int s = sys_of_row(e_off, nsys, p);
+        const int64_t c0 = zcol_off[s];
+        const int r = (int)(zcol_off[s + 1] - c0);
+        const int64_t loc = p - e_off[s];
+        const int a = (int)(loc / r), k = (int)(loc % r);
+        const int col = (int)(c0 + k);
+        double acc = 0.0;
+        const int q1 = ztrp[c0 + a + 1];
 #pragma unroll 4
-    for (int q = ztrp[c0 + a] + ln; q < q1; q += kWave) {
-        const int i = ztci[q];
-        for (int t = azrp[i]; t < azrp[i + 1]; ++t)
-            if (azci[t] == col) acc += ztv[q] * azv[t];
+        for (int q = ztrp[c0 + a] + ln; q < q1; q += kWave) {
+            const int i = ztci[q];
+            for (int t = azrp[i]; t < azrp[i + 1]; ++t)
+                if (azci[t] == col) acc += ztv[q] * azv[t];
+        }
+        acc = gwave_sum(acc);
+        if (ln == 0) E[p] = acc;
     }
-    acc = gwave_sum(acc);
-    if (ln == 0) E[p] = acc;
 }
 
 void build_coarse(const SetupArgs& a, const int* ztrp, const int* ztci, const double* ztv,
@@ -518,9 +522,10 @@ void build_coarse(const SetupArgs& a, const int* ztrp, const int* ztci, const do
     int64_t total = 0;
     hipMemcpyAsync(&total, d_e_off + a.nsys, sizeof(int64_t), hipMemcpyDeviceToHost, a.st);
     hipStreamSynchronize(a.st);
+    const int64_t grid = std::min((total + kWG / kWave - 1) / (kWG / kWave), kEGrid);
     if (total > 0)
-        k_build_e<<<blocks_for(total * kWave), kWG, 0, a.st>>>(a.nsys, a.d_sys_zcol_off, d_e_off, ztrp, ztci,
-                                                      ztv, azrp, azci, azv, E);
+        k_build_e<<<(unsigned)grid, kWG, 0, a.st>>>(a.nsys, a.d_sys_zcol_off, d_e_off, ztrp, ztci, ztv, azrp,
+                                                   azci, azv, E);
 }
 
 // LU with partial pivoting of each E_s (row-major, in place; one workgroup per
