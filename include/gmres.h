@@ -318,6 +318,16 @@ gmres_status gmres_autotune(gmres_plan p, int32_t* chosen_h);
 gmres_status gmres_set_timing(gmres_plan p, int32_t period);
 gmres_status gmres_kernel_times(gmres_plan p, double* out_h /* 24 doubles */);
 
+/* Which kernels this plan's solves ran on, counted since setup (an inner solve
+ * of a mixed-precision refinement and a whole batch count as one each; the
+ * continuation of a batched system counts on its own plan):
+ * out_h[0] solves in one cooperative launch of workgroups that stay on the
+ * chip together (one launch a cycle with adaptive deflation), out_h[1] solves
+ * such a launch gave up, each repeated on the other kernels, out_h[2] solves on
+ * the kernel-per-phase engine, or batches with one workgroup per system.
+ * Block solves are not counted. */
+gmres_status gmres_gang_counts(gmres_plan p, int64_t* out_h /* 3 */);
+
 /* Switches the stream used by later calls. */
 gmres_status gmres_set_stream(gmres_plan p, hipStream_t stream);
 

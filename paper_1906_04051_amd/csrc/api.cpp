@@ -173,6 +173,9 @@ struct gmres_plan_s {
     // system order, then abort word, tickets and published system indices
     int gang_nwg = 0, gang_ncls = 0, gang_vcap = 0, gang_ecap = 0;
     int *gang_sched = nullptr, *gang_words = nullptr;
+    // Solves (inner solves, batches) that ran in gang launches, that a launch
+    // gave up, and that ran on the other kernels (gmres_gang_counts).
+    int64_t gang_counts[3] = {0, 0, 0};
     double *tpart = nullptr, *s_step = nullptr, *s_res = nullptr;
     Ctrl* ctrl = nullptr;
     Ctrl* ctrl_h = nullptr;             // pinned, 2 snapshots
@@ -957,6 +960,7 @@ gmres_status engine_ahead(EngineRun& r) {
 gmres_status engine_start(EngineRun& r, const void* b, double rtol, double r0_override, int64_t max_iters,
                           bool trust_est) {
     gmres_plan_s* p = r.p;
+    ++p->gang_counts[2];
     r.a = make_args(p, r.op, r.prec);
     r.a.trust_est = trust_est ? 1 : 0;
     r.at = r.a;
@@ -1162,12 +1166,16 @@ gmres_status run_gang(gmres_plan_s* p, int op, int prec, const void* b, double r
         HIP_OK(hipMemcpyAsync(&p->ctrl_h[0], p->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, p->st));
         HIP_OK(hipStreamSynchronize(p->st));
         *out = p->ctrl_h[0];
-        if (out->pad32 != 0) return GMRES_OK;
+        if (out->pad32 != 0) {
+            ++p->gang_counts[1];
+            return GMRES_OK;
+        }
         if (out->done) break;
         if (a.ast) adapt_cycle_end(make_args(p, op, prec), static_cast<const double*>(p->V), p->coef1);
         a.resume = 1;
     }
     p->hist_pos += out->its;
+    ++p->gang_counts[0];
     *ran = true;
     return GMRES_OK;
 }
@@ -2056,6 +2064,7 @@ static gmres_status run_batch_gangs(gmres_plan_s* p, const double* b, const doub
     int aborted = 0;
     HIP_OK(hipMemcpyAsync(&aborted, p->gang_words, sizeof(int), hipMemcpyDeviceToHost, p->st));
     HIP_OK(hipStreamSynchronize(p->st));
+    ++p->gang_counts[aborted ? 1 : 0];
     *ran = aborted == 0;
     return GMRES_OK;
 }
@@ -2351,7 +2360,10 @@ gmres_status gmres_solve_batched(gmres_plan p, const double* b, const double* x0
         xs = p->btune_x;
     }
     CHECK(run_batch_gangs(p, b, xs, x, &ran));
-    if (!ran) CHECK(run_batched(p, b, xs, x, p->o.max_iters, p->batch_wg, p->batch_L));
+    if (!ran) {
+        ++p->gang_counts[2];
+        CHECK(run_batched(p, b, xs, x, p->o.max_iters, p->batch_wg, p->batch_L));
+    }
     const int ns = p->nsys;
     double* nr = p->bout_d + 4 * (int64_t)ns;
     std::vector<int64_t> oi(3 * (size_t)ns);
@@ -2551,6 +2563,12 @@ gmres_status gmres_set_timing(gmres_plan p, int32_t period) {
     if (period < 0) return fail(GMRES_EINVAL, "timing period must be >= 0");
     p->timer.period = period;
     p->timer.reset();
+    return GMRES_OK;
+}
+
+gmres_status gmres_gang_counts(gmres_plan p, int64_t* out_h) {
+    if (!p || !out_h) return fail(GMRES_EINVAL, "plan and out_h are required");
+    for (int k = 0; k < 3; ++k) out_h[k] = p->gang_counts[k];
     return GMRES_OK;
 }
 

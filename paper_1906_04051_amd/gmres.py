@@ -28,8 +28,8 @@ EXPORTS = ["gmres_default_opts", "gmres_workspace_bytes", "gmres_workspace_requi
            "gmres_solve_block",
            "gmres_solve_block_noalloc",
            "gmres_adjoint", "gmres_update_values", "gmres_spmv", "gmres_history",
-           "gmres_autotune", "gmres_set_timing", "gmres_kernel_times", "gmres_set_stream",
-           "gmres_destroy", "gmres_last_error"]
+           "gmres_autotune", "gmres_set_timing", "gmres_kernel_times", "gmres_gang_counts",
+           "gmres_set_stream", "gmres_destroy", "gmres_last_error"]
 
 
 class GmresOpts(C.Structure):
@@ -100,6 +100,7 @@ def load_library():
     lib.gmres_autotune.argtypes = [vp, C.POINTER(i32)]
     lib.gmres_set_timing.argtypes = [vp, i32]
     lib.gmres_kernel_times.argtypes = [vp, C.POINTER(dbl)]
+    lib.gmres_gang_counts.argtypes = [vp, C.POINTER(i64)]
     lib.gmres_set_stream.argtypes = [vp, vp]
     lib.gmres_destroy.argtypes = [vp]
     lib.gmres_destroy.restype = None
@@ -108,7 +109,7 @@ def load_library():
     for name in ("gmres_setup", "gmres_solve", "gmres_solve_batched", "gmres_batched_attach", "gmres_solve_block",
                  "gmres_solve_block_noalloc", "gmres_adjoint",
                  "gmres_update_values", "gmres_spmv", "gmres_autotune", "gmres_set_timing",
-                 "gmres_kernel_times", "gmres_set_stream"):
+                 "gmres_kernel_times", "gmres_gang_counts", "gmres_set_stream"):
         getattr(lib, name).restype = C.c_int
     _lib = lib
     return lib
@@ -330,6 +331,14 @@ class Plan:
         names = ["spmv", "pass1", "pass2", "pass3", "pass1_lag", "block_dots", "block_gemm", "block_spmm"]
         return {nm: dict(launches=out[3 * k], ms=out[3 * k + 1], bytes=out[3 * k + 2])
                 for k, nm in enumerate(names)}
+
+    def gang_counts(self) -> dict:
+        """Solves since setup by the kernels they ran on: in cooperative
+        launches of resident workgroups (gang), given up there and repeated
+        (given_up), on the other kernels (other)."""
+        out = (C.c_int64 * 3)()
+        _check(self._lib.gmres_gang_counts(self._h, out))
+        return dict(gang=out[0], given_up=out[1], other=out[2])
 
 
 def upload(sysm, device="cuda"):

@@ -1,0 +1,117 @@
+"""Which kernels a solve runs on (gmres_gang_counts): whole solves in
+cooperative launches (gang.hip) where the plan's options leave the choice to
+the library and the system fits, with no launch given up; the kernel-per-phase
+engine (or one workgroup per system of a batch) where an option asks for it or
+the system is too large.  The comparisons of test_gpu_gang.py compare the two
+only if this holds."""
+import numpy as np
+import pytest
+
+from paper_1906_04051_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+GANG = dict(gang=1, given_up=0, other=0)
+OTHER = dict(gang=0, given_up=0, other=1)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU visible")
+    from paper_1906_04051_amd import gmres as G
+    G.load_library()
+    yield
+
+
+def _plan(mesh, s=0, **opts):
+    from paper_1906_04051_amd import gmres as G
+    return G.plan_for(W.convection_diffusion_manufactured(mesh, s=s), **opts)
+
+
+FIXED = dict(m=12, rtol=0.0, max_iters=20)
+
+
+@pytest.mark.parametrize("mesh,s,opts", [
+    (15, 0, FIXED),
+    (16, 2, FIXED),
+    (100, 16, FIXED),
+    (254, 4, FIXED),
+    (256, 8, dict(m=80, rtol=0.0, max_iters=90)),
+    (362, 8, FIXED),
+    (512, 4, FIXED),
+    (100, 4, dict(FIXED, spmv_lanes=-64)),
+    (100, 4, dict(FIXED, record_history=1)),
+    (100, 4, dict(FIXED, use_graph=0)),
+    (40, 0, dict(FIXED, adapt_rmax=3)),
+    (512, 0, dict(FIXED, adapt_rmax=3)),
+])
+def test_solves_in_one_launch(mesh, s, opts):
+    plan, d = _plan(mesh, s, **opts)
+    plan.solve(d["b"])
+    assert plan.gang_counts() == GANG
+    plan.close()
+
+
+@pytest.mark.parametrize("mesh,opts", [
+    (100, dict(num_blocks=64)),
+    (100, dict(spmv_lanes=8)),
+    (100, dict(spmv_lanes=-256)),
+    (100, dict(ortho=0)),
+    (100, dict(ortho=2)),
+    (100, dict(adapt_rmax=3, num_blocks=64)),
+    (800, dict()),            # 641,601 rows
+])
+def test_solves_on_the_engine(mesh, opts):
+    plan, d = _plan(mesh, **FIXED, **opts)
+    plan.solve(d["b"])
+    assert plan.gang_counts() == OTHER
+    plan.close()
+
+
+def test_timed_solves_run_on_the_engine():
+    plan, d = _plan(100, 4, **FIXED)
+    plan.set_timing(1)
+    plan.solve(d["b"])
+    assert plan.gang_counts() == OTHER
+    plan.set_timing(0)
+    plan.solve(d["b"])
+    assert plan.gang_counts() == dict(gang=1, given_up=0, other=1)
+    plan.close()
+
+
+@pytest.mark.parametrize("prec,mesh", [("mixed_f32", 90), ("mixed_f16", 90), ("mixed_f32", 627), ("mixed_f16", 513)])
+def test_inner_solves_in_one_launch(prec, mesh):
+    plan, d = _plan(mesh, 8, m=30, rtol=1e-9, max_iters=100000, precision=prec)
+    _, info = plan.solve(d["b"])
+    assert plan.gang_counts() == dict(gang=info["refinements"], given_up=0, other=0)
+    plan.close()
+
+
+def test_adjoint_in_one_launch():
+    plan, d = _plan(64, 4, need_adjoint=True, m=30, rtol=1e-10)
+    x, _ = plan.solve(d["b"])
+    plan.adjoint(x, torch.ones_like(x))
+    assert plan.gang_counts() == dict(gang=2, given_up=0, other=0)
+    plan.close()
+
+
+def test_rows_past_nine_entries_in_one_launch():
+    from paper_1906_04051_amd import gmres as G
+    plan, d = G.plan_for(W.make_config(3, mesh=40), **FIXED)
+    plan.solve(d["b"])
+    assert plan.gang_counts() == GANG
+    plan.close()
+
+
+@pytest.mark.parametrize("lo,hi,ns,s,m", [(16, 40, 5, 2, 30), (24, 90, 6, 0, 64), (16, 96, 40, 4, 30),
+                                          (230, 256, 3, 4, 10)])
+def test_batches(lo, hi, ns, s, m):
+    from paper_1906_04051_amd import gmres as G
+    batch = W.make_batch(ns, lo, hi, s)
+    for kw, want in ((dict(), GANG), (dict(batch_wg=256), OTHER), (dict(batch_lanes=8), OTHER)):
+        plan, d = G.plan_for(batch, m=m, rtol=0.0, max_iters=20, **kw)
+        plan.solve_batched(d["b"])
+        assert plan.gang_counts() == want, kw
+        plan.close()
