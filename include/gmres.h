@@ -328,6 +328,17 @@ gmres_status gmres_kernel_times(gmres_plan p, double* out_h /* 24 doubles */);
  * Block solves are not counted. */
 gmres_status gmres_gang_counts(gmres_plan p, int64_t* out_h /* 3 */);
 
+/* Solves in one cooperative launch need a place on the chip for all of their
+ * workgroups at once (up to one per compute unit, with most of its LDS).  Beside
+ * a kernel of another stream or process that keeps them from it, the launch is
+ * given up after start_us microseconds (default 10,000) and the solve repeated
+ * on the other kernels; the next solves leave the launch out, 1, 2, 4, ... up to
+ * 64 of them after launches given up in a row.  wait_us (default 2,000,000): the
+ * same limit for the waits of workgroups that are all on the chip.  start_us <
+ * 0: no such launches.  Both solves build the same Krylov spaces and agree to
+ * rounding.  EINVAL for values above 1e9, a negative wait_us or a NaN. */
+gmres_status gmres_set_gang_wait(gmres_plan p, double start_us, double wait_us);
+
 /* Switches the stream used by later calls. */
 gmres_status gmres_set_stream(gmres_plan p, hipStream_t stream);
 

@@ -176,6 +176,12 @@ struct gmres_plan_s {
     // Solves (inner solves, batches) that ran in gang launches, that a launch
     // gave up, and that ran on the other kernels (gmres_gang_counts).
     int64_t gang_counts[3] = {0, 0, 0};
+    // Limits of a gang's waits, us (gmres_set_gang_wait; start < 0: no gangs).
+    // After a launch was given up the next gang_skip solves run on the other
+    // kernels, twice as many each time in a row, so a chip that stays busy
+    // costs few waits.
+    double gang_start_us = 10e3, gang_wait_us = 2e6;
+    int gang_skip = 0, gang_backoff = 0;
     double *tpart = nullptr, *s_step = nullptr, *s_res = nullptr;
     Ctrl* ctrl = nullptr;
     Ctrl* ctrl_h = nullptr;             // pinned, 2 snapshots
@@ -1037,6 +1043,30 @@ gmres_status run_engine(gmres_plan_s* p, int op, int prec, const void* b, double
     return engine_end(r, out);
 }
 
+// Limits of a gang launch's waits in ticks of the 100 MHz device clock; a wait
+// looks at them, and whether another workgroup has given up, after 1 ms.
+void gang_limits(const gmres_plan_s* p, GangHot& h, GangArgs& a) {
+    a.start_ticks = (long long)(100.0 * p->gang_start_us);
+    a.wait_ticks = (long long)(100.0 * p->gang_wait_us);
+    h.look = (int)std::min<long long>(std::min(a.start_ticks, a.wait_ticks), 100000);
+}
+
+// False while launches are left out (see gang_skip); call once a solve.
+bool gang_allowed(gmres_plan_s* p) {
+    if (p->gang_start_us < 0) return false;
+    if (p->gang_skip == 0) return true;
+    --p->gang_skip;
+    return false;
+}
+
+// Counts a launch that ran to its end or was given up.
+void gang_ended(gmres_plan_s* p, bool ran) {
+    constexpr int kMaxSkip = 64;
+    ++p->gang_counts[ran ? 0 : 1];
+    p->gang_backoff = ran ? 0 : std::min(std::max(1, 2 * p->gang_backoff), kMaxSkip);
+    p->gang_skip = p->gang_backoff;
+}
+
 // Launch shape of a gang solve (gang.hip) for one engine, or K = 0 where the
 // kernel-per-phase engine runs: an explicit SpMV, grid or orthogonalisation
 // choice, kernel timing, no sliced-ELL copy, or a size past the lines below.
@@ -1141,7 +1171,7 @@ gmres_status run_gang(gmres_plan_s* p, int op, int prec, const void* b, double r
                       int64_t max_iters, bool trust_est, double* xout, Ctrl* out, bool* ran) {
     *ran = false;
     const GangShape g = gang_shape(p, op, prec);
-    if (g.K == 0) return GMRES_OK;
+    if (g.K == 0 || !gang_allowed(p)) return GMRES_OK;
     TraceRange tr_("gang solve");
     GangHot h{};
     GangArgs a{};
@@ -1149,6 +1179,7 @@ gmres_status run_gang(gmres_plan_s* p, int op, int prec, const void* b, double r
     h.K = g.K;
     h.vcap = g.vcap;
     h.ecap = g.ecap;
+    gang_limits(p, h, a);
     a.trust_est = trust_est ? 1 : 0;
     a.max_iters = max_iters;
     a.rtol = rtol;
@@ -1167,7 +1198,7 @@ gmres_status run_gang(gmres_plan_s* p, int op, int prec, const void* b, double r
         HIP_OK(hipStreamSynchronize(p->st));
         *out = p->ctrl_h[0];
         if (out->pad32 != 0) {
-            ++p->gang_counts[1];
+            gang_ended(p, false);
             return GMRES_OK;
         }
         if (out->done) break;
@@ -1175,7 +1206,7 @@ gmres_status run_gang(gmres_plan_s* p, int op, int prec, const void* b, double r
         a.resume = 1;
     }
     p->hist_pos += out->its;
-    ++p->gang_counts[0];
+    gang_ended(p, true);
     *ran = true;
     return GMRES_OK;
 }
@@ -2008,7 +2039,7 @@ static gmres_status plan_batch_gangs(gmres_plan_s* p) {
 // schedule, the launch was refused or a rendezvous timed out.
 static gmres_status run_batch_gangs(gmres_plan_s* p, const double* b, const double* x0, double* x, bool* ran) {
     *ran = false;
-    if (p->gang_nwg == 0 || p->ncont > 0) return GMRES_OK;
+    if (p->gang_nwg == 0 || p->ncont > 0 || !gang_allowed(p)) return GMRES_OK;
     GangHot h{};
     h.m = p->o.m;
     h.ecap = p->gang_ecap;
@@ -2026,6 +2057,7 @@ static gmres_status run_batch_gangs(gmres_plan_s* p, const double* b, const doub
     h.tpart = p->gang_tpart;
     GangArgs a{};
     a.st = p->st;
+    gang_limits(p, h, a);
     a.max_cycles = INT32_MAX;
     a.max_iters = p->o.max_iters;
     a.rtol = p->o.rtol;
@@ -2064,8 +2096,8 @@ static gmres_status run_batch_gangs(gmres_plan_s* p, const double* b, const doub
     int aborted = 0;
     HIP_OK(hipMemcpyAsync(&aborted, p->gang_words, sizeof(int), hipMemcpyDeviceToHost, p->st));
     HIP_OK(hipStreamSynchronize(p->st));
-    ++p->gang_counts[aborted ? 1 : 0];
     *ran = aborted == 0;
+    gang_ended(p, *ran);
     return GMRES_OK;
 }
 
@@ -2563,6 +2595,16 @@ gmres_status gmres_set_timing(gmres_plan p, int32_t period) {
     if (period < 0) return fail(GMRES_EINVAL, "timing period must be >= 0");
     p->timer.period = period;
     p->timer.reset();
+    return GMRES_OK;
+}
+
+gmres_status gmres_set_gang_wait(gmres_plan p, double start_us, double wait_us) {
+    if (!p) return fail(GMRES_EINVAL, "plan is NULL");
+    if (!(start_us <= 1e9) || !(wait_us >= 0 && wait_us <= 1e9))
+        return fail(GMRES_EINVAL, "start_us <= 1e9 and 0 <= wait_us <= 1e9 required");
+    p->gang_start_us = start_us;
+    p->gang_wait_us = wait_us;
+    p->gang_skip = p->gang_backoff = 0;
     return GMRES_OK;
 }
 

@@ -22,9 +22,18 @@
 // iterate, partial sums, flags) is stored and loaded with relaxed agent-scope
 // atomics, which go past the per-die L2s, and every wave waits for its stores
 // (vmcnt(0)) before its workgroup's flag is set; nothing else is shared, so no
-// cache is written back or invalidated and the matrix stays in L2.  A poll
-// gives up after kSpinTicks: the launch then ends with the abort word set and
-// the host repeats the solve on the kernel-per-phase engine.
+// cache is written back or invalidated and the matrix stays in L2.
+//
+// Every wait ends.  The launch does not push other kernels off the chip: beside
+// a kernel of another stream or process that holds compute units, workgroups
+// may have to wait for a place while the others poll.  The first rendezvous,
+// which shows that all of the gang is there, therefore gives up after
+// start_ticks (10 ms by default), any later one, which only a fault or a
+// preempted queue can hold up, after wait_ticks (2 s); a wait longer than
+// 1 ms also ends when the abort word shows that another workgroup has
+// given up.  The launch then ends with that word set, and the host repeats the
+// solve on the kernel-per-phase engine and leaves the gang out of the next
+// solves.
 //
 // Adaptive deflation (MODE == kGangAdapt; adapt.hip): M^{-1} changes at every
 // restart and its update needs the basis, so a launch runs one cycle.  Within
@@ -41,7 +50,6 @@ namespace gm {
 
 constexpr int kGN = 512;                      // threads per workgroup
 constexpr int kGW = kGN / kWave;              // wavefronts
-constexpr long long kSpinTicks = 200000000;   // 2 s at the 100 MHz wall clock
 
 // Pointers with their address space spelled out: accesses that could go to
 // either memory must not be merged into flat ones.
@@ -133,15 +141,21 @@ __device__ __forceinline__ void gang_arrive(int K, int me, unsigned* flags, unsi
     __syncthreads();
     if (K > 1 && threadIdx.x == 0) st_ag(flags + me * kFlagW, epoch);
 }
+// A wait of `waited` ticks has to end (epoch 1: the gang's first rendezvous);
+// nothing is loaded before the wait has lasted h.look ticks.
+__device__ __forceinline__ bool gang_expired(long long waited, const GangHot& h, const GangArgs& a, unsigned epoch) {
+    return waited > h.look && (waited > (epoch == 1 ? a.start_ticks : a.wait_ticks) || ld_ag(a.abortw) != 0);
+}
 // Waits until every member of the gang shows `epoch`; false (in every thread)
 // after a timeout.
-__device__ __forceinline__ bool gang_wait(int K, const unsigned* flags, unsigned epoch, int* s_abort) {
+__device__ __forceinline__ bool gang_wait(int K, const unsigned* flags, unsigned epoch, int* s_abort,
+                                          const GangHot& h, const GangArgs& a) {
     if (K == 1) return true;
     if ((int)threadIdx.x < K) {
         const unsigned* f = flags + threadIdx.x * kFlagW;
         const long long t0 = wall_clock64();
         while ((int)(ld_ag(f) - epoch) < 0) {
-            if (wall_clock64() - t0 > kSpinTicks) {
+            if (gang_expired(wall_clock64() - t0, h, a, epoch)) {
                 *s_abort = 1;
                 break;
             }
@@ -158,7 +172,7 @@ __device__ __forceinline__ bool gang_wait(int K, const unsigned* flags, unsigned
     } while (0)
 #define GANG_WAIT()                                                \
     do {                                                           \
-        if (!gang_wait(K, flags, epoch, s_abort)) GANG_FAIL();     \
+        if (!gang_wait(K, flags, epoch, s_abort, h, a)) GANG_FAIL(); \
     } while (0)
 
 // Sums travel without flags: an entry that is not there yet holds a
@@ -180,7 +194,7 @@ __device__ __forceinline__ void st_empty(double* p) {
 // the wave's sums go to redrow.
 template <int W>
 __device__ __forceinline__ void gang_rows(int nc, const double* part, int ps, int K, int wv, int ln,
-                                          double* redrow, int* s_abort) {
+                                          double* redrow, int* s_abort, const GangHot& h, const GangArgs& a) {
     constexpr int MPL = kWave / W, U = 8;
     const int col = min(ln & (W - 1), nc - 1), sub = ln / W;
     double t = 0;
@@ -197,7 +211,7 @@ __device__ __forceinline__ void gang_rows(int nc, const double* part, int ps, in
             if (!__any(wait)) break;
             const long long now = wall_clock64();
             if (t0 == 0) t0 = now;
-            if (now - t0 > kSpinTicks) {
+            if (gang_expired(now - t0, h, a, 0)) {
                 *s_abort = 1;
                 break;
             }
@@ -264,8 +278,10 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
     int slot = 0, pslot = 0, pcount = 0, tslot = 0, tpend = -1;
     unsigned* bmap = a.bmap + (int64_t)first * 8;
 
-    if (tid == 0) *s_abort = 0;
+    // A workgroup that finds a place after the others have given up leaves.
+    if (tid == 0) *s_abort = (int)ld_ag(a.abortw);
     __syncthreads();
+    if (uni(*s_abort)) return;
 
     for (;;) {
         // ---- next system
@@ -274,9 +290,10 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
         int c0 = 0;
         if constexpr (BATCH) {
             if (me == 0 && tid == 0) {
-                // Own class first, then the classes of smaller gangs.
+                // Own class first, then the classes of smaller gangs; none
+                // once a gang has given up (the batch is repeated).
                 int s = -1;
-                for (int c = a.wg_class[blockIdx.x]; c < a.ncls && s < 0; ++c) {
+                for (int c = ld_ag(a.abortw) ? a.ncls : a.wg_class[blockIdx.x]; c < a.ncls && s < 0; ++c) {
                     const int q = a.cls_ptr[c] + atomicAdd(a.ticket + c, 1);
                     if (q < a.cls_ptr[c + 1]) s = a.order[q];
                 }
@@ -651,7 +668,7 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                         if (!wait) break;
                         const long long now = wall_clock64();
                         if (t0 == 0) t0 = now;
-                        if (now - t0 > kSpinTicks) {
+                        if (gang_expired(now - t0, h, a, 0)) {
                             *s_abort = 1;
                             break;
                         }
@@ -855,9 +872,9 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                 const double* part = ring + slot * K * ps;
                 for (int c = 0; c < nc; c += kWave) {
                     const int left = nc - c;
-                    if (left > 32) gang_rows<64>(left, part + c, ps, K, wv, ln, grow[wv] + c, s_abort);
-                    else if (left > 16) gang_rows<32>(left, part + c, ps, K, wv, ln, grow[wv] + c, s_abort);
-                    else gang_rows<16>(left, part + c, ps, K, wv, ln, grow[wv] + c, s_abort);
+                    if (left > 32) gang_rows<64>(left, part + c, ps, K, wv, ln, grow[wv] + c, s_abort, h, a);
+                    else if (left > 16) gang_rows<32>(left, part + c, ps, K, wv, ln, grow[wv] + c, s_abort, h, a);
+                    else gang_rows<16>(left, part + c, ps, K, wv, ln, grow[wv] + c, s_abort, h, a);
                 }
                 __syncthreads();
                 if (tid < nc) {

@@ -301,6 +301,7 @@ struct GangHot {
     int m, n, R, K, Rmax;
     int vcap, ecap;           // LDS bytes for the basis and for rows of E^{-1}
     int trans, wuni;
+    int look;                 // ticks after which a wait looks at its limit and the abort word
     const int *sell_off, *perm;
     const short* sell_col;
     const void* sell_val;
@@ -323,6 +324,7 @@ struct GangArgs {
     const void* b;
     double *xh, *xout;
     unsigned *abortw, *bmap;
+    long long start_ticks, wait_ticks;   // limits of the first wait and of the others (100 MHz)
     // single system: state and records
     Ctrl* ctrl;
     double* hist;

@@ -29,7 +29,7 @@ EXPORTS = ["gmres_default_opts", "gmres_workspace_bytes", "gmres_workspace_requi
            "gmres_solve_block_noalloc",
            "gmres_adjoint", "gmres_update_values", "gmres_spmv", "gmres_history",
            "gmres_autotune", "gmres_set_timing", "gmres_kernel_times", "gmres_gang_counts",
-           "gmres_set_stream", "gmres_destroy", "gmres_last_error"]
+           "gmres_set_gang_wait", "gmres_set_stream", "gmres_destroy", "gmres_last_error"]
 
 
 class GmresOpts(C.Structure):
@@ -101,6 +101,7 @@ def load_library():
     lib.gmres_set_timing.argtypes = [vp, i32]
     lib.gmres_kernel_times.argtypes = [vp, C.POINTER(dbl)]
     lib.gmres_gang_counts.argtypes = [vp, C.POINTER(i64)]
+    lib.gmres_set_gang_wait.argtypes = [vp, dbl, dbl]
     lib.gmres_set_stream.argtypes = [vp, vp]
     lib.gmres_destroy.argtypes = [vp]
     lib.gmres_destroy.restype = None
@@ -109,7 +110,7 @@ def load_library():
     for name in ("gmres_setup", "gmres_solve", "gmres_solve_batched", "gmres_batched_attach", "gmres_solve_block",
                  "gmres_solve_block_noalloc", "gmres_adjoint",
                  "gmres_update_values", "gmres_spmv", "gmres_autotune", "gmres_set_timing",
-                 "gmres_kernel_times", "gmres_gang_counts", "gmres_set_stream"):
+                 "gmres_kernel_times", "gmres_gang_counts", "gmres_set_gang_wait", "gmres_set_stream"):
         getattr(lib, name).restype = C.c_int
     _lib = lib
     return lib
@@ -331,6 +332,11 @@ class Plan:
         names = ["spmv", "pass1", "pass2", "pass3", "pass1_lag", "block_dots", "block_gemm", "block_spmm"]
         return {nm: dict(launches=out[3 * k], ms=out[3 * k + 1], bytes=out[3 * k + 2])
                 for k, nm in enumerate(names)}
+
+    def set_gang_wait(self, start_us: float = 10e3, wait_us: float = 2e6):
+        """Limits of the waits of solves in one cooperative launch
+        (gmres_set_gang_wait); start_us < 0: no such launches."""
+        _check(self._lib.gmres_set_gang_wait(self._h, float(start_us), float(wait_us)))
 
     def gang_counts(self) -> dict:
         """Solves since setup by the kernels they ran on: in cooperative
