@@ -1272,6 +1272,12 @@ gmres_status leave(gmres_plan_s* p) {
     return GMRES_OK;
 }
 
+// Some of n doubles at a are among the n at b.
+bool overlap(const double* a, const double* b, int64_t n) {
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p < q + n * sizeof(double) && q < p + n * sizeof(double);
+}
+
 // FP64 solve of op (0: A, 1: A^T) for right-hand side b (device, n) from x0
 // (or zero) into x.  Fills info (iters/cycles/status/rho0/rel_res).
 gmres_status solve_f64(gmres_plan_s* p, int op, const double* b, const double* x0, double* x,
@@ -1285,9 +1291,10 @@ gmres_status solve_f64(gmres_plan_s* p, int op, const double* b, const double* x
     Ctrl c{};
     bool ran = false;
     if (op == 0 && p->adapt.rmax > 0) adapt_reset(p->st, p->adapt);   // U starts empty
-    // With a start vector (which x may be) the result passes through r64, so a
-    // repeat on the per-phase engine still finds x0.
-    double* xo = x0 ? p->r64 : x;
+    // With a start vector (which x may be), or where x reaches into b, the
+    // result passes through r64: when some workgroups have written theirs and
+    // the launch is given up after all, the repeat still finds x0 and b.
+    double* xo = x0 || overlap(x, b, n) ? p->r64 : x;
     CHECK(run_gang(p, op, kPrecF64, b, rtol, r0_override, max_iters, false, xo, &c, &ran));
     if (ran) {
         if (xo != x) launch_copy(p->st, xo, x, n);

@@ -182,3 +182,23 @@ def test_solves_beside_a_chip_filling_batch():
     assert done and all(i["status_name"] == "OK" for i in done[0])
     plan.close()
     bplan.close()
+
+
+@pytest.mark.parametrize("limits", [dict(), AT_START, INSIDE, NEVER], ids=["gang", "start", "inside", "engine"])
+@pytest.mark.parametrize("shift", [-700, 700])
+def test_x_may_reach_into_b(limits, shift):
+    """x and b are ranges of one buffer (they may not start together): the
+    solution is that of separate buffers, and nothing of the right-hand side is
+    written before the iteration has read it for the last time."""
+    from paper_1906_04051_amd import gmres as G
+    sysm = _system(100, 4)
+    plan, d = G.plan_for(sysm, m=20, rtol=0.0, max_iters=50)
+    plan.set_gang_wait(**limits)
+    ref, _ = plan.solve(d["b"])
+    plan.set_gang_wait(**limits)
+    buf = torch.zeros(sysm.n + 1400, dtype=torch.float64, device="cuda")
+    buf[700:700 + sysm.n] = d["b"]
+    x = buf[700 + shift:700 + shift + sysm.n]
+    plan.solve(buf[700:700 + sysm.n], out=x)
+    assert torch.equal(x, ref)
+    plan.close()
