@@ -1272,17 +1272,24 @@ __global__ void k_gang_clear(GangArgs a, GangArgs* dst, unsigned* flags, int nwg
 }
 
 // ------------------------------------------------------------------------ host
+// The kernel for rpt row slots a thread, or null where no rule launches it: a
+// batch's gangs have rows for one slot, three is the most for FP64, four for
+// the reduced precisions.
 template <typename AT, typename VT, typename WT, typename BT, typename ACC, int MODE>
 static const void* gang_fn(int rpt, bool w9) {
     if (rpt == 1)
         return w9 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 1, 9, MODE>
                   : (const void*)k_gang<AT, VT, WT, BT, ACC, 1, 0, MODE>;
-    if (rpt == 2)
-        return w9 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 2, 9, MODE>
-                  : (const void*)k_gang<AT, VT, WT, BT, ACC, 2, 0, MODE>;
-    // No registers left for the matrix.
-    return rpt == 3 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 3, 0, MODE>
-                    : (const void*)k_gang<AT, VT, WT, BT, ACC, 4, 0, MODE>;
+    if constexpr (MODE != kGangBatch) {
+        if (rpt == 2)
+            return w9 ? (const void*)k_gang<AT, VT, WT, BT, ACC, 2, 9, MODE>
+                      : (const void*)k_gang<AT, VT, WT, BT, ACC, 2, 0, MODE>;
+        // No registers left for the matrix.
+        if (rpt == 3) return (const void*)k_gang<AT, VT, WT, BT, ACC, 3, 0, MODE>;
+        if constexpr (sizeof(VT) < 8)
+            if (rpt == 4) return (const void*)k_gang<AT, VT, WT, BT, ACC, 4, 0, MODE>;
+    }
+    return nullptr;
 }
 
 size_t gang_lds_fixed(int m, int prec) {
@@ -1302,6 +1309,7 @@ bool launch_gang(const GangHot& h0, const GangArgs& a, void* args_d, int prec, i
                     : prec == kPrecF64 ? gang_fn<double, double, double, double, double, kGangSingle>(rpt, w9)
                     : prec == kPrecF32 ? gang_fn<float, float, float, float, float, kGangSingle>(rpt, w9)
                                        : gang_fn<float, __half, float, float, float, kGangSingle>(rpt, w9);
+    if (!f) return false;
     const size_t dynb = 8 * (size_t)gang_hraw(h.m) + h.ecap + h.vcap;
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dynb) != hipSuccess) {
         (void)hipGetLastError();

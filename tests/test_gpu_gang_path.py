@@ -115,3 +115,27 @@ def test_batches(lo, hi, ns, s, m):
         plan.solve_batched(d["b"])
         assert plan.gang_counts() == want, kw
         plan.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed_f32", "mixed_f16"])
+@pytest.mark.parametrize("mesh", [140, 200, 256])
+def test_wide_rows_in_every_row_slot(mesh, prec):
+    """Rows of 9 to 25 entries with one, two and three row slots a thread
+    (78,961, 160,801 and 263,169 rows): the gang's iterate or solution is the
+    engine's (fixed count: rounding over 20 steps, the 1e-8 of the other
+    trajectory tests; mixed: both residuals at 1e-10 of ||b||, and ||A^{-1}|| ||b||
+    / ||x||, 6.8 at 20 elements a side, belongs to the continuous problem)."""
+    from paper_1906_04051_amd import gmres as G
+    s = W.make_config(3, mesh=mesh)
+    kw = dict(FIXED) if prec == "fp64" else dict(m=20, rtol=1e-10, precision=prec)
+    out = []
+    for extra in (dict(), dict(num_blocks=256)):
+        plan, d = G.plan_for(s, **kw, **extra)
+        x, info = plan.solve(d["b"])
+        out.append(x)
+        c = plan.gang_counts()
+        assert c["given_up"] == 0 and c["gang" if not extra else "other"] == max(1, info["refinements"]), c
+        if prec != "fp64":
+            assert info["rel_res_true"] <= 1e-10
+        plan.close()
+    assert float((out[0] - out[1]).norm() / out[1].norm()) <= 1e-8
