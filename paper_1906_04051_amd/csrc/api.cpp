@@ -1067,17 +1067,43 @@ void gang_ended(gmres_plan_s* p, bool ran) {
     p->gang_skip = p->gang_backoff;
 }
 
+// Most basis bytes a workgroup for which a gang beats the engine.  A gang's
+// step grows with the columns that lie past LDS (0.055 us a KB, read twice a
+// step), the engine's hardly (a basis of these sizes stays in the last-level
+// cache); the engine's grows with a deflation basis (two coarse solves a pair)
+// and with its columns.  The lines were fitted to 283 pairs of measurements
+// (66,049 to 524,176 rows, m = 30 to 96, no to 256 columns): the slower path is
+// taken for at most 5% more time, except a basis of a single column (24%).
+// us per step, gang / engine, either side of the line:
+//   FP64, no columns: 262,144 rows, m = 30 (240 KB) 25.5 / 32.8, m = 50 (400 KB)
+//   35.7 / 34.1, m = 80 51.4 / 38.5; 64 columns: 361,201 rows, m = 30 (345 KB)
+//   42.7 / 50.7, m = 50 (575 KB) 54.8 / 52.4; 271,441 rows, m = 80 63.0 / 52.4;
+//   256 columns: 271,441 rows, m = 80 (680 KB) 67.5 / 72.7.
+//   FP32, no columns: 262,144 rows, m = 50 (200 KB) 20.1 / 24.5, m = 80 30.8 /
+//   28.5; 524,176 rows, m = 80 59.3 / 36.6; 64 columns: 410,881 rows, m = 50
+//   (325 KB) 45.1 / 45.7, m = 80 59.5 / 53.1.
+//   FP16, no columns: 361,201 rows, m = 50 (143 KB) 24.7 / 24.9, m = 80 35.4 /
+//   28.1; 64 columns: 410,881 rows, m = 50 (162 KB) 37.6 / 43.1, m = 80 50.0 / 49.0.
+// With the adaptive deflation the engine takes one step per pair of sweeps:
+// 393,129 rows, m = 50 (600 KB) 62.3 / 78.9.  700 KB: no measurements above.
+int64_t gang_basis_limit(int prec, int64_t rw, int R, bool adaptive) {
+    struct Line {
+        double base, per_row, some_z, per_col;   // KB; per_col: for each column past 64
+    };
+    const Line l = prec == kPrecF64   ? Line{270, 0.1, 90, 1.5}
+                   : prec == kPrecF32 ? Line{200, 0.0, 160, 1.5}
+                                      : Line{60, 0.05, 120, 0.5};
+    const double kb = l.base + l.per_row * (double)rw + (R > 0 ? l.some_z : 0.0) + l.per_col * std::max(0, R - 64);
+    return (int64_t)(1024.0 * (adaptive ? 700.0 : std::min(kb, 700.0)));
+}
+
 // Launch shape of a gang solve (gang.hip) for one engine, or K = 0 where the
 // kernel-per-phase engine runs: an explicit SpMV, grid or orthogonalisation
-// choice, kernel timing, no sliced-ELL copy, or a size past the lines below.
-// 256 rows a workgroup (a wavefront per SIMD) until every compute unit has one.  Measured, us per step, gang / engine:
-//   FP64, 64 indicators: 66,049 rows, m = 50: 19.5 / 46; 263,169, m = 30:
-//   38 / 62; 361,201, m = 50 (589 KB of basis a workgroup): 58 / 72, m = 80
-//   (942 KB): 91 / 88; 491,401 (four rows a thread, spills), m = 30: 69 / 72,
-//   m = 50: 91 / 83.
-//   FP32 basis: 491,401 rows, m = 50: 49 / 63, m = 80 (635 KB): 65 / 72;
-//   FP16 basis, m = 50: 41 / 55.
-// Hence the limits of 700 KB of basis and of three (FP64) or four row slots.
+// choice, kernel timing, no sliced-ELL copy, or a size past the lines above and
+// below: three row slots a thread in FP64 (four spill: 491,401 rows, m = 50, 91
+// us a step against 83 of the engine without pairs), four in the reduced
+// precisions.  256 rows a workgroup (a wavefront per SIMD) until every compute
+// unit has one.  66,049 rows, 64 columns, m = 50: 19.3 us a step, the engine 35.5.
 struct GangShape {
     int K = 0, rpt = 0, vcap = 0, ecap = 0;
     bool w9 = false;
@@ -1100,7 +1126,8 @@ GangShape gang_shape(const gmres_plan_s* p, int op, int prec) {
     rw = (rw + 63) & ~int64_t(63);
     const int vb = prec == kPrecF64 ? 8 : prec == kPrecF32 ? 4 : 2;
     const int64_t full = rw * p->o.m * vb;
-    if (rw > (prec == kPrecF64 ? 3 : 4) * kGangRows || full > 700 * 1024) return g;
+    const bool adaptive = p->adapt.rmax > 0 && op == 0 && prec == kPrecF64;
+    if (rw > (prec == kPrecF64 ? 3 : 4) * kGangRows || full > gang_basis_limit(prec, rw, p->R, adaptive)) return g;
     g.ecap = (int)std::min<int64_t>(8 * (int64_t)p->R * p->R, 16384);
     const size_t fixed = gang_lds_fixed(p->o.m, prec) + (size_t)g.ecap;
     if (fixed >= (size_t)lds_max) return g;

@@ -139,3 +139,31 @@ def test_wide_rows_in_every_row_slot(mesh, prec):
             assert info["rel_res_true"] <= 1e-10
         plan.close()
     assert float((out[0] - out[1]).norm() / out[1].norm()) <= 1e-8
+
+
+@pytest.mark.parametrize("prec,mesh,s,m,gang", [
+    ("fp64", 511, 0, 46, True),           # 368 KB of basis a workgroup, limit 372
+    ("fp64", 511, 0, 47, False),
+    ("fp64", 511, 8, 57, True),           # 456 of 462
+    ("fp64", 511, 8, 58, False),
+    ("fp64", 511, 16, 87, True),          # 696 of 700 (the line: 750)
+    ("fp64", 511, 16, 88, False),
+    ("mixed_f32", 511, 0, 50, True),      # 200 of 200
+    ("mixed_f32", 511, 0, 51, False),
+    ("mixed_f16", 511, 0, 55, True),      # 110 of 111
+    ("mixed_f16", 511, 0, 56, False),
+    ("adaptive", 511, 0, 87, True),
+    ("adaptive", 511, 0, 88, False),
+])
+def test_the_size_rule(prec, mesh, s, m, gang):
+    """Both sides of each line (1,024 rows a workgroup): the same solution
+    (one step to check the path; mixed: an inner tolerance any step meets)."""
+    opts = dict(m=m, rtol=0.0, max_iters=1)
+    if prec == "adaptive":
+        opts["adapt_rmax"] = 3
+    elif prec != "fp64":
+        opts.update(precision=prec, max_refine=1, inner_max_iters=1, rtol=1e-8)
+    plan, d = _plan(mesh, s, **opts)
+    plan.solve(d["b"])
+    assert plan.gang_counts() == (GANG if gang else OTHER)
+    plan.close()
