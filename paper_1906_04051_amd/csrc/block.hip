@@ -209,7 +209,8 @@ __global__ __launch_bounds__(kWG) void k_bnorm(int64_t n, int pw, const double* 
 // entries are in flight meanwhile.  1,050,625 rows of 9, 16 columns: 182 us
 // (MODE 0) and 265 (MODE 1) with a column a lane and rows dealt round the dies,
 // 152 and 187 with two columns a lane, 130 and 155 with the entries staged
-// (368 MB: 75 us at the rate of a copy).
+// (368 MB: 75 us at the rate of a copy).  A stage holds 32 entries a row: of
+// longer rows it holds a few whole ones, and the lanes of the others wait.
 template <int PW>
 constexpr int kSpRows = kWG / (PW / 2);
 constexpr int kSpC = 9;        // gathers in flight a lane (a whole Q1 row)
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(kWG) void k_bspmm(int64_t n, int rounds, const int*
                                                const double* __restrict__ B, double* __restrict__ Y,
                                                double* __restrict__ part, const int* __restrict__ stop) {
     constexpr int lpr = PW / 2, rpr = kSpRows<PW>;
-    constexpr int NL = 32 / lpr, cap = NL * kWave;   // entries a lane, a wavefront (16 a row)
+    constexpr int NL = 32 / lpr, cap = NL * kWave;   // entries a lane, a wavefront (32 a row)
     __shared__ int sc[kWG / kWave][cap];
     __shared__ double sv[kWG / kWave][cap];
     __shared__ double red[2 * kWG];
@@ -305,6 +306,64 @@ __global__ __launch_bounds__(kWG) void k_bspmm(int64_t n, int rounds, const int*
     if (MODE == 1) {
         red[2 * threadIdx.x] = n0;
         red[2 * threadIdx.x + 1] = n1;
+        __syncthreads();
+        if (threadIdx.x < kBW) {
+            double s = 0.0;
+            if (threadIdx.x < PW)
+                for (int i = 0; i < rpr; ++i) s += red[i * PW + threadIdx.x];
+            part[(int64_t)blockIdx.x * kBW + threadIdx.x] = s;
+        }
+    }
+}
+
+// The same with PW lanes per row, a column each, that read their row's entries
+// themselves: every row of a workgroup advances at once, whatever its length,
+// and nothing is staged before the first gather.
+template <int MODE, int PW>
+__global__ __launch_bounds__(kWG) void k_bspmm_rows(int64_t n, const int* __restrict__ rowptr,
+                                                    const int* __restrict__ colind,
+                                                    const double* __restrict__ vals,
+                                                    const double* __restrict__ X,
+                                                    const double* __restrict__ B, double* __restrict__ Y,
+                                                    double* __restrict__ part, const int* __restrict__ stop) {
+    __shared__ double red[kWG];
+    if (stop && *stop) return;   // a later step of a cycle that has ended
+    constexpr int rpr = kWG / PW;
+    const int c = threadIdx.x & (PW - 1), rl = threadIdx.x / PW;
+    double nrm = 0.0;
+    for (int64_t r0 = (int64_t)blockIdx.x * rpr; r0 < n; r0 += (int64_t)gridDim.x * rpr) {
+        const int64_t row = r0 + rl;
+        if (row < n) {
+            const int q0 = rowptr[row], q1 = rowptr[row + 1];
+            double acc = 0.0;
+            int q = q0;
+            for (; q + 4 <= q1; q += 4) {
+                const int c0 = colind[q], c1 = colind[q + 1], c2 = colind[q + 2], c3 = colind[q + 3];
+                GM_DCHECK(min(min(c0, c1), min(c2, c3)) >= 0 && max(max(c0, c1), max(c2, c3)) < n,
+                          kDbgBlockCol);
+                const double a0 = vals[q], a1 = vals[q + 1], a2 = vals[q + 2], a3 = vals[q + 3];
+                const double x0 = X[(int64_t)c0 * PW + c], x1 = X[(int64_t)c1 * PW + c];
+                const double x2 = X[(int64_t)c2 * PW + c], x3 = X[(int64_t)c3 * PW + c];
+                acc += a0 * x0;
+                acc += a1 * x1;
+                acc += a2 * x2;
+                acc += a3 * x3;
+            }
+            for (; q < q1; ++q) {
+                GM_DCHECK(colind[q] >= 0 && colind[q] < n, kDbgBlockCol);
+                acc += vals[q] * X[(int64_t)colind[q] * PW + c];
+            }
+            if (MODE == 0) {
+                Y[row * PW + c] = acc;
+            } else {
+                const double y = B[row * PW + c] - acc;
+                Y[row * PW + c] = y;
+                nrm += y * y;
+            }
+        }
+    }
+    if (MODE == 1) {
+        red[threadIdx.x] = nrm;
         __syncthreads();
         if (threadIdx.x < kBW) {
             double s = 0.0;
@@ -1281,13 +1340,32 @@ double spmm_bytes(const BlockWork& w, const BlockArgs& a, int mode) {
     return 12.0 * (double)a.nnz + 4.0 * (double)(w.n + 1) + (2.0 + mode) * (double)w.n * w.pw * sizeof(double);
 }
 
-// Y = A X (mode 0, up to kSpRounds
-// rounds a workgroup while kNormGrid of them are left) or Y = B - A X with column
-// partial sums of squares (mode 1, kNormGrid workgroups), the instance for the
-// solve's panel width.
+// Whether the SpMM stages its entries (k_bspmm) or its rows read them
+// (k_bspmm_rows), by the mean row length and the work.  us a product, rows /
+// staged, 16 columns: 8,000 rows of 9: 4.8 / 5.3, of 17: 7.3 / 6.2; 250,000 of 9:
+// 32.4 / 26.1, of 33: 115 / 62; past the 32 entries a stage holds of a row, 20,000
+// of 41: 15.5 / 17.9, of 151: 44.5 / 102; 60,000 of 65: 58.1 / 52.8, of 101: 85.1 /
+// 106.  8 columns: 20,000 of 33: 10.3 / 11.1; 60,000 of 17: 12.2 / 9.9, of 65: 33.3 /
+// 35.3; 250,000 of 9: 16.9 / 17.2, of 65: 134 / 127, of 101: 215 / 269.
+template <int PW>
+bool spmm_staged(int64_t n, int64_t nnz) {
+    constexpr int64_t kEntries = PW == 8 ? 900000 : 100000, kRowsLong = PW == 8 ? 200000 : 60000;
+    return nnz >= kEntries && (nnz <= 33 * n || (nnz <= 66 * n && n >= kRowsLong));
+}
+
+// Y = A X (mode 0; staged: up to kSpRounds rounds a workgroup while kNormGrid of
+// them are left) or Y = B - A X with column partial sums of squares (mode 1,
+// kNormGrid workgroups), the instance for the solve's panel width.
 template <int MODE, int PW>
 void spmm_pw(const BlockWork& w, const BlockArgs& a, const double* X, const double* B, double* Y, double* part,
              const int* stop) {
+    if (!spmm_staged<PW>(w.n, a.nnz)) {
+        constexpr int64_t rows = kWG / PW;
+        blaunch(a.timer, 7, spmm_bytes(w, a, MODE), k_bspmm_rows<MODE, PW>,
+                dim3((unsigned)(MODE == 0 ? (w.n + rows - 1) / rows : kNormGrid)), dim3(kWG), a.st, w.n, a.rowptr,
+                a.colind, a.vals, X, B, Y, part, stop);
+        return;
+    }
     constexpr int64_t rpr = kSpRows<PW>;
     const int64_t rounds = MODE == 0 ? std::max<int64_t>(1, std::min<int64_t>(kSpRounds, w.n / (kNormGrid * rpr)))
                                      : (w.n + kNormGrid * rpr - 1) / (kNormGrid * rpr);
