@@ -321,22 +321,24 @@ gmres_status gmres_kernel_times(gmres_plan p, double* out_h /* 24 doubles */);
 /* Which kernels this plan's solves ran on, counted since setup (an inner solve
  * of a mixed-precision refinement and a whole batch count as one each; the
  * continuation of a batched system counts on its own plan):
- * out_h[0] solves in one cooperative launch of workgroups that stay on the
- * chip together (one launch a cycle with adaptive deflation), out_h[1] solves
- * such a launch gave up, each repeated on the other kernels, out_h[2] solves on
- * the kernel-per-phase engine, or batches with one workgroup per system.
- * Block solves are not counted. */
+ * out_h[0] solves in one launch of workgroups that stay on the chip together
+ * (one launch a cycle with adaptive deflation), out_h[1] solves such a launch
+ * gave up, each repeated on the other kernels, out_h[2] solves on the
+ * kernel-per-phase engine, or batches with one workgroup per system.  Block
+ * solves are not counted. */
 gmres_status gmres_gang_counts(gmres_plan p, int64_t* out_h /* 3 */);
 
-/* Solves in one cooperative launch need a place on the chip for all of their
- * workgroups at once (up to one per compute unit, with most of its LDS).  Beside
- * a kernel of another stream or process that keeps them from it, the launch is
- * given up after start_us microseconds (default 10,000) and the solve repeated
- * on the other kernels; the next solves leave the launch out, 1, 2, 4, ... up to
- * 64 of them after launches given up in a row.  wait_us (default 2,000,000): the
- * same limit for the waits of workgroups that are all on the chip.  start_us <
- * 0: no such launches.  Both solves build the same Krylov spaces and agree to
- * rounding.  EINVAL for values above 1e9, a negative wait_us or a NaN. */
+/* Solves in one launch need a place on the chip for all of their workgroups at
+ * once (up to one per compute unit, with most of its LDS).  Beside such solves of
+ * other threads of the process a solve waits for its place on the host, beside a
+ * kernel of another stream or process its workgroups wait on the chip, each at
+ * most start_us microseconds (default 10,000).  Then the solve runs on the other
+ * kernels, and after a launch that was given up the next solves leave the
+ * launch out, 1, 2, 4, ... up to 64 of them after launches given up in a row.
+ * wait_us (default 2,000,000): the same limit for the waits of workgroups that
+ * are all on the chip.  start_us < 0: no such launches.  Both solves build the
+ * same Krylov spaces and agree to rounding.  EINVAL for values above 1e9, a
+ * negative wait_us or a NaN. */
 gmres_status gmres_set_gang_wait(gmres_plan p, double start_us, double wait_us);
 
 /* Switches the stream used by later calls. */

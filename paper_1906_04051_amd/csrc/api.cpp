@@ -1105,7 +1105,7 @@ int64_t gang_basis_limit(int prec, int64_t rw, int R, bool adaptive) {
 // precisions.  256 rows a workgroup (a wavefront per SIMD) until every compute
 // unit has one.  66,049 rows, 64 columns, m = 50: 19.3 us a step, the engine 35.5.
 struct GangShape {
-    int K = 0, rpt = 0, vcap = 0, ecap = 0;
+    int cus = 0, K = 0, rpt = 0, vcap = 0, ecap = 0;
     bool w9 = false;
 };
 
@@ -1132,6 +1132,7 @@ GangShape gang_shape(const gmres_plan_s* p, int op, int prec) {
     const size_t fixed = gang_lds_fixed(p->o.m, prec) + (size_t)g.ecap;
     if (fixed >= (size_t)lds_max) return g;
     g.vcap = (int)std::min<int64_t>(full, (int64_t)lds_max - (int64_t)fixed);
+    g.cus = cus;
     g.K = (int)((n + rw - 1) / rw);
     g.rpt = (int)((rw + kGangRows - 1) / kGangRows);
     g.w9 = (op ? p->tsell_wmax : p->sell_wmax) <= 9;
@@ -1199,6 +1200,8 @@ gmres_status run_gang(gmres_plan_s* p, int op, int prec, const void* b, double r
     *ran = false;
     const GangShape g = gang_shape(p, op, prec);
     if (g.K == 0 || !gang_allowed(p)) return GMRES_OK;
+    GangPlace place;
+    if (!place.take(p->device, g.cus, g.K, p->gang_start_us)) return GMRES_OK;
     TraceRange tr_("gang solve");
     GangHot h{};
     GangArgs a{};
@@ -2069,11 +2072,15 @@ static gmres_status plan_batch_gangs(gmres_plan_s* p) {
     return GMRES_OK;
 }
 
-// The batch as gangs in one cooperative launch; *ran = false where it has no
+// The batch as gangs in one launch; *ran = false where it has no
 // schedule, the launch was refused or a rendezvous timed out.
 static gmres_status run_batch_gangs(gmres_plan_s* p, const double* b, const double* x0, double* x, bool* ran) {
     *ran = false;
     if (p->gang_nwg == 0 || p->ncont > 0 || !gang_allowed(p)) return GMRES_OK;
+    int cus = 0;
+    HIP_OK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+    GangPlace place;
+    if (!place.take(p->device, cus, p->gang_nwg, p->gang_start_us)) return GMRES_OK;
     GangHot h{};
     h.m = p->o.m;
     h.ecap = p->gang_ecap;

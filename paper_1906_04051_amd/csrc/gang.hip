@@ -1,7 +1,7 @@
-// Whole deflated GMRES(m) solves in one persistent cooperative launch.
+// Whole deflated GMRES(m) solves in one persistent launch.
 //
-// A gang of K workgroups (one per compute unit, all resident: cooperative
-// launch) owns a system: workgroup `me` owns a contiguous range of RW sliced
+// A gang of K workgroups (one per compute unit, all on the chip together) owns
+// a system: workgroup `me` owns a contiguous range of RW sliced
 // positions, one thread per row.  The Krylov basis of those rows lives in the
 // workgroup's LDS (columns that do not fit there in global memory, read only
 // by their owner), so the two Gram-Schmidt sweeps of a step touch no HBM.
@@ -24,16 +24,20 @@
 // (vmcnt(0)) before its workgroup's flag is set; nothing else is shared, so no
 // cache is written back or invalidated and the matrix stays in L2.
 //
-// Every wait ends.  The launch does not push other kernels off the chip: beside
-// a kernel of another stream or process that holds compute units, workgroups
-// may have to wait for a place while the others poll.  The first rendezvous,
-// which shows that all of the gang is there, therefore gives up after
-// start_ticks (10 ms by default), any later one, which only a fault or a
-// preempted queue can hold up, after wait_ticks (2 s); a wait longer than
-// 1 ms also ends when the abort word shows that another workgroup has
-// given up.  The launch then ends with that word set, and the host repeats the
-// solve on the kernel-per-phase engine and leaves the gang out of the next
-// solves.
+// All of a gang has to be on the chip.  It is an ordinary launch on the plan's
+// stream (a cooperative one would take one of the process's four hardware
+// queues for good: 25 systems continued on their own streams then took 1,080 ms
+// instead of 745), so the host keeps the gangs of this process apart: a launch
+// holds as many compute units of every die as its workgroups need there
+// (GangPlace), and one that does not fit beside the others waits for them.
+// Kernels of other streams or processes that hold compute units are not in that
+// account, so every wait in the kernel ends: the first rendezvous, which shows
+// that all of the gang is there, gives up after start_ticks (10 ms by default),
+// any later one, which only a fault or a preempted queue can hold up, after
+// wait_ticks (2 s); a wait longer than 1 ms also ends when the abort word shows
+// that another workgroup has given up.  The launch then ends with that word set,
+// and the host repeats the solve on the kernel-per-phase engine and leaves the
+// gang out of the next solves.
 //
 // Adaptive deflation (MODE == kGangAdapt; adapt.hip): M^{-1} changes at every
 // restart and its update needs the basis, so a launch runs one cycle.  Within
@@ -45,6 +49,10 @@
 // 22 columns: 32 us a step, Ritz steps included, 67 on the per-phase engine;
 // 361,201 rows, m = 30: 63 / 101.
 #include "internal.hpp"
+
+#include <chrono>
+#include <condition_variable>
+#include <mutex>
 
 namespace gm {
 
@@ -1301,6 +1309,40 @@ size_t gang_lds_fixed(int m, int prec) {
 
 size_t gang_args_bytes() { return sizeof(GangArgs); }
 
+// Compute units of every die that the process's gangs hold, per device.
+namespace {
+struct Chip {
+    std::mutex mu;
+    std::condition_variable cv;
+    int used = 0;
+};
+Chip g_chip[64];
+}  // namespace
+
+bool GangPlace::take(int device, int cus, int nwg, double wait_us) {
+    if (device < 0 || device >= 64 || units_ > 0) return false;
+    // Workgroups go round the dies, so a die gets at most one more than another.
+    const int cap = std::max(1, cus / kXcd), need = std::min((nwg + kXcd - 1) / kXcd, cap);
+    Chip& c = g_chip[device];
+    std::unique_lock<std::mutex> lk(c.mu);
+    if (!c.cv.wait_for(lk, std::chrono::duration<double, std::micro>(wait_us), [&] { return c.used + need <= cap; }))
+        return false;
+    c.used += need;
+    device_ = device;
+    units_ = need;
+    return true;
+}
+
+GangPlace::~GangPlace() {
+    if (units_ == 0) return;
+    Chip& c = g_chip[device_];
+    {
+        std::lock_guard<std::mutex> lk(c.mu);
+        c.used -= units_;
+    }
+    c.cv.notify_all();
+}
+
 bool launch_gang(const GangHot& h0, const GangArgs& a, void* args_d, int prec, int rpt, bool w9, int nwg,
                  int nticket) {
     GangHot h = h0;
@@ -1319,7 +1361,7 @@ bool launch_gang(const GangHot& h0, const GangArgs& a, void* args_d, int prec, i
     k_gang_clear<<<1, 256, 0, a.st>>>(a, ad, h.flags, nwg, nticket);
     const GangArgs* ac = ad;
     void* args[] = {&h, &ac};
-    if (hipLaunchCooperativeKernel(f, dim3(nwg), dim3(kGN), args, (unsigned)dynb, a.st) != hipSuccess) {
+    if (hipLaunchKernel(f, dim3(nwg), dim3(kGN), args, dynb, a.st) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }

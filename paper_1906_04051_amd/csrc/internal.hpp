@@ -293,7 +293,7 @@ inline int64_t block_slots_bound(int64_t n, int RB, int R, int64_t znnz) {
 }
 
 // gang.hip
-// One cooperative launch of gangs of workgroups (see gang.hip).  Single
+// One launch of gangs of workgroups that are on the chip together (see gang.hip).  Single
 // system: row_off = nullptr, one gang of K workgroups; batch: wg_* give every
 // workgroup's gang (member, size, queue class) and each class its systems.
 // What the step loop reads goes by value, the rest lies in device memory.
@@ -353,6 +353,21 @@ size_t gang_args_bytes();
 constexpr int kGangFlagWords = 32;   // words between the workgroups' flags (a cache line each)
 // Row stride (doubles) of a workgroup's partial sums: whole cache lines.
 __host__ __device__ constexpr int gang_ps(int cols) { return (cols + 15) & ~15; }
+// The compute units that a gang launch of nwg workgroups holds until the object
+// goes (after the launch has ended).  take: false when the gangs of other
+// threads leave too few for wait_us microseconds.
+class GangPlace {
+public:
+    GangPlace() = default;
+    GangPlace(const GangPlace&) = delete;
+    GangPlace& operator=(const GangPlace&) = delete;
+    ~GangPlace();
+    bool take(int device, int cus, int nwg, double wait_us);
+
+private:
+    int device_ = 0, units_ = 0;
+};
+
 // False when the launch was refused (the caller uses the per-phase engine).
 // args_d: gang_args_bytes() of device memory.
 bool launch_gang(const GangHot& h, const GangArgs& a, void* args_d, int prec, int rpt, bool w9, int nwg,

@@ -334,14 +334,14 @@ class Plan:
                 for k, nm in enumerate(names)}
 
     def set_gang_wait(self, start_us: float = 10e3, wait_us: float = 2e6):
-        """Limits of the waits of solves in one cooperative launch
+        """Limits of the waits of solves in one launch
         (gmres_set_gang_wait); start_us < 0: no such launches."""
         _check(self._lib.gmres_set_gang_wait(self._h, float(start_us), float(wait_us)))
 
     def gang_counts(self) -> dict:
-        """Solves since setup by the kernels they ran on: in cooperative
-        launches of resident workgroups (gang), given up there and repeated
-        (given_up), on the other kernels (other)."""
+        """Solves since setup by the kernels they ran on: in launches of
+        workgroups that are on the chip together (gang), given up there and
+        repeated (given_up), on the other kernels (other)."""
         out = (C.c_int64 * 3)()
         _check(self._lib.gmres_gang_counts(self._h, out))
         return dict(gang=out[0], given_up=out[1], other=out[2])

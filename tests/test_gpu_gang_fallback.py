@@ -1,4 +1,4 @@
-"""Cooperative launches that are given up (gang.hip): limits of microseconds,
+"""Launches that are given up (gang.hip): limits of microseconds,
 set from the host, make a wait of the launch give up -- at its first rendezvous
 or in the middle of the iteration -- and every kernel ends normally.  The solve
 is then repeated on the other kernels from the caller's own data: the result
@@ -202,3 +202,49 @@ def test_x_may_reach_into_b(limits, shift):
     plan.solve(buf[700:700 + sysm.n], out=x)
     assert torch.equal(x, ref)
     plan.close()
+
+
+def test_gangs_that_do_not_fit_together_wait_for_each_other():
+    """Five threads whose gangs take 207 or 256 compute units each, with
+    places for one, and a batch: nobody's workgroups wait on the chip in vain
+    (a second is enough for all that is in front of a thread)."""
+    from paper_1906_04051_amd import gmres as G
+    jobs = []
+    for mesh, s, m in ((256, 8, 20), (256, 0, 30), (300, 4, 20), (400, 2, 20)):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            plan, d = G.plan_for(_system(mesh, s), m=m, rtol=0.0, max_iters=40, stream=st)
+        jobs.append([st, plan, d, lambda plan=plan, d=d: plan.solve(d["b"])[0]])
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        plan, d = G.plan_for(W.make_batch(40, 16, 96, 4), m=20, rtol=0.0, max_iters=40, stream=st)
+    jobs.append([st, plan, d, lambda plan=plan, d=d: plan.solve_batched(d["b"])[0]])
+    torch.cuda.synchronize()
+    refs, got = [], [None] * len(jobs)
+    for j in jobs:
+        j[1].set_gang_wait(start_us=1e6)
+        with torch.cuda.stream(j[0]):
+            refs.append(j[3]().clone())
+
+    def work(i):
+        with torch.cuda.stream(jobs[i][0]):
+            try:
+                got[i] = [jobs[i][3]().clone() for _ in range(12)]
+            except Exception as e:   # seen by the assertion below
+                got[i] = e
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(len(jobs))]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    torch.cuda.synchronize()
+    for j, ref, g in zip(jobs, refs, got):
+        assert isinstance(g, list), g
+        assert j[1].gang_counts() == dict(gang=13, given_up=0, other=0)
+        # A system of the batch may be taken by a larger gang than before.
+        if j is jobs[-1]:
+            assert all(float((x - ref).norm() / ref.norm()) <= 1e-8 for x in g)
+        else:
+            assert all(torch.equal(x, ref) for x in g)
+        j[1].close()

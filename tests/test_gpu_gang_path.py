@@ -1,5 +1,5 @@
 """Which kernels a solve runs on (gmres_gang_counts): whole solves in
-cooperative launches (gang.hip) where the plan's options leave the choice to
+one launch (gang.hip) where the plan's options leave the choice to
 the library and the system fits, with no launch given up; the kernel-per-phase
 engine (or one workgroup per system of a batch) where an option asks for it or
 the system is too large.  The comparisons of test_gpu_gang.py compare the two

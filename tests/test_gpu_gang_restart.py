@@ -56,8 +56,10 @@ def test_restarts_repeat_bit_for_bit(mesh, s, m, steps):
 
 
 def test_batch_restarts_repeat_bit_for_bit():
+    """Systems of one size: whichever gang takes one, it has the same number of
+    workgroups."""
     from paper_1906_04051_amd import gmres as G
-    batch = W.make_batch(24, 16, 96, 4)
+    batch = W.make_batch(24, 96, 96, 4)
     plan, d = G.plan_for(batch, m=3, rtol=0.0, max_iters=60)
     first = None
     for _ in range(REPEATS):
