@@ -170,7 +170,8 @@ struct gmres_plan_s {
     char* gang_args = nullptr;
     // batch in gangs: workgroups of the launch (0: one workgroup a system),
     // classes, LDS split; wg_member / wg_size / wg_class, class pointers,
-    // system order, then abort word, tickets and published system indices
+    // system order, workgroups of each system; then abort word, tickets and
+    // published system indices
     int gang_nwg = 0, gang_ncls = 0, gang_vcap = 0, gang_ecap = 0;
     int *gang_sched = nullptr, *gang_words = nullptr;
     // Solves (inner solves, batches) that ran in gang launches, that a launch
@@ -432,7 +433,7 @@ void carve_batched(gmres_plan_s* p, Arena& A) {
     }
     if (ns > 1) {
         carve_gang(p, A);
-        p->gang_sched = A.take_n<int>(3 * kGangWG + kGangCls + 1 + ns);
+        p->gang_sched = A.take_n<int>(3 * kGangWG + kGangCls + 1 + 2 * ns);
         p->gang_words = A.take_n<int>(1 + kGangCls + kGangWG);
     }
     p->bW = A.take_n<double>(3 * padded);
@@ -2053,7 +2054,7 @@ static gmres_status plan_batch_gangs(gmres_plan_s* p) {
     const int ecap = (int)std::min<int64_t>(8 * rmax * rmax, 16384);
     const int64_t fixed = (int64_t)gang_lds_fixed(p->o.m, kPrecF64) + ecap;
     if (fixed >= lds_max) return GMRES_OK;
-    std::vector<int> sched(3 * kGangWG + kGangCls + 1 + ns, 0);
+    std::vector<int> sched(3 * kGangWG + kGangCls + 1 + 2 * ns, 0);
     int wg = 0;
     for (int c = 0; c < nc; ++c)
         for (int k = 0; k < gangs[c]; ++k)
@@ -2064,6 +2065,8 @@ static gmres_status plan_batch_gangs(gmres_plan_s* p) {
             }
     std::copy(ptr.begin(), ptr.end(), sched.begin() + 3 * kGangWG);
     std::copy(order.begin(), order.end(), sched.begin() + 3 * kGangWG + kGangCls + 1);
+    for (int c = 0; c < nc; ++c)
+        for (int q = ptr[c]; q < ptr[c + 1]; ++q) sched[3 * kGangWG + kGangCls + 1 + ns + order[q]] = size[c];
     HIP_OK(hipMemcpy(p->gang_sched, sched.data(), sched.size() * sizeof(int), hipMemcpyHostToDevice));
     p->gang_ecap = ecap;
     p->gang_vcap = (int)std::min<int64_t>(rw_max * p->o.m * 8, lds_max - fixed);
@@ -2126,6 +2129,7 @@ static gmres_status run_batch_gangs(gmres_plan_s* p, const double* b, const doub
     a.wg_class = p->gang_sched + 2 * kGangWG;
     a.cls_ptr = p->gang_sched + 3 * kGangWG;
     a.order = p->gang_sched + 3 * kGangWG + kGangCls + 1;
+    a.sys_size = a.order + p->nsys;
     a.row_off = p->d_row_off;
     a.zcol_off = p->d_zcol_off;
     a.e_off = p->d_e_off;

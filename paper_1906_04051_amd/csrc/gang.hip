@@ -149,21 +149,24 @@ __device__ __forceinline__ void gang_arrive(int K, int me, unsigned* flags, unsi
     __syncthreads();
     if (K > 1 && threadIdx.x == 0) st_ag(flags + me * kFlagW, epoch);
 }
-// A wait of `waited` ticks has to end (epoch 1: the gang's first rendezvous);
-// nothing is loaded before the wait has lasted h.look ticks.
-__device__ __forceinline__ bool gang_expired(long long waited, const GangHot& h, const GangArgs& a, unsigned epoch) {
-    return waited > h.look && (waited > (epoch == 1 ? a.start_ticks : a.wait_ticks) || ld_ag(a.abortw) != 0);
+// A wait of `waited` ticks has to end; nothing is loaded before it has lasted
+// h.look ticks.  kWaitSystem: members of a batch's gang that have no part in its
+// system wait for the others, who end it or give up.
+constexpr int kWaitSum = 0, kWaitStart = 1, kWaitSystem = 2;
+__device__ __forceinline__ bool gang_expired(long long waited, const GangHot& h, const GangArgs& a, int kind) {
+    return waited > h.look && ((kind != kWaitSystem && waited > (kind == kWaitStart ? a.start_ticks : a.wait_ticks)) ||
+                               ld_ag(a.abortw) != 0);
 }
 // Waits until every member of the gang shows `epoch`; false (in every thread)
 // after a timeout.
 __device__ __forceinline__ bool gang_wait(int K, const unsigned* flags, unsigned epoch, int* s_abort,
-                                          const GangHot& h, const GangArgs& a) {
+                                          const GangHot& h, const GangArgs& a, int kind) {
     if (K == 1) return true;
     if ((int)threadIdx.x < K) {
         const unsigned* f = flags + threadIdx.x * kFlagW;
         const long long t0 = wall_clock64();
         while ((int)(ld_ag(f) - epoch) < 0) {
-            if (gang_expired(wall_clock64() - t0, h, a, epoch)) {
+            if (gang_expired(wall_clock64() - t0, h, a, kind)) {
                 *s_abort = 1;
                 break;
             }
@@ -178,10 +181,11 @@ __device__ __forceinline__ bool gang_wait(int K, const unsigned* flags, unsigned
         if (tid == 0) st_ag(a.abortw, 1u);    \
         return;                               \
     } while (0)
-#define GANG_WAIT()                                                \
-    do {                                                           \
-        if (!gang_wait(K, flags, epoch, s_abort, h, a)) GANG_FAIL(); \
+#define GANG_WAIT_FOR(K_, kind)                                                   \
+    do {                                                                          \
+        if (!gang_wait(K_, flags, epoch, s_abort, h, a, kind)) GANG_FAIL();       \
     } while (0)
+#define GANG_WAIT() GANG_WAIT_FOR(K, epoch == 1 ? kWaitStart : kWaitSum)
 
 // Sums travel without flags: an entry that is not there yet holds a
 // signalling NaN, which no arithmetic result is (operations return quiet
@@ -219,7 +223,7 @@ __device__ __forceinline__ void gang_rows(int nc, const double* part, int ps, in
             if (!__any(wait)) break;
             const long long now = wall_clock64();
             if (t0 == 0) t0 = now;
-            if (gang_expired(now - t0, h, a, 0)) {
+            if (gang_expired(now - t0, h, a, kWaitSum)) {
                 *s_abort = 1;
                 break;
             }
@@ -271,9 +275,12 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
 
     // ---- gang membership
     const int me = BATCH ? uni(a.wg_member[blockIdx.x]) : (int)blockIdx.x;
-    const int K = BATCH ? uni(a.wg_size[blockIdx.x]) : h.K;
+    const int Kg = BATCH ? uni(a.wg_size[blockIdx.x]) : h.K;
     const int first = (int)blockIdx.x - me;
     unsigned epoch = 0;
+    // Published systems alternate between two words: a member without a part
+    // in a system may read its word while the leader publishes the next one.
+    int turn = 0;
     unsigned* flags = h.flags + first * kFlagW;
     const int ps = gang_ps(m + 2 + (ADAPT ? kAU : 0)), ts = gang_ps(h.Rmax);   // row strides
     // Exchange e of the gang uses slot e % 3: a workgroup empties its row of
@@ -293,7 +300,7 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
 
     for (;;) {
         // ---- next system
-        int sys = 0, n = h.n, R = h.R;
+        int sys = 0, n = h.n, R = h.R, K = Kg;
         int64_t r0 = 0;
         int c0 = 0;
         if constexpr (BATCH) {
@@ -306,14 +313,23 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                     if (q < a.cls_ptr[c + 1]) s = a.order[q];
                 }
                 si[4] = s;
-                if (K > 1) st_ag((int*)a.next_sys + first, s);
+                if (Kg > 1) st_ag((int*)a.next_sys + first + turn, s);
             }
             GANG_ARRIVE();
-            GANG_WAIT();
-            if (K > 1 && tid == 0 && me != 0) si[4] = ld_ag((const int*)a.next_sys + first);
+            GANG_WAIT_FOR(Kg, epoch == 1 ? kWaitStart : kWaitSystem);
+            if (Kg > 1 && tid == 0 && me != 0) si[4] = ld_ag((const int*)a.next_sys + first + turn);
+            turn ^= 1;
             __syncthreads();
             sys = uni(si[4]);
             if (sys < 0) return;
+            // A system is split over the gang size of its own class whichever
+            // gang takes it, so its sums have one order and a repeated batch has
+            // the same bits; a larger gang's other members wait.
+            K = uni(a.sys_size[sys]);
+            if (me >= K) {
+                epoch += a.zcol_off[sys + 1] > a.zcol_off[sys] ? 2 : 1;   // the rendezvous of its start
+                continue;
+            }
             r0 = uni64(a.row_off[sys]);
             n = uni((int)(a.row_off[sys + 1] - r0));
             c0 = uni((int)a.zcol_off[sys]);
@@ -676,7 +692,7 @@ __global__ __launch_bounds__(kGN) void k_gang(GangHot h, const GangArgs* ac) {
                         if (!wait) break;
                         const long long now = wall_clock64();
                         if (t0 == 0) t0 = now;
-                        if (gang_expired(now - t0, h, a, 0)) {
+                        if (gang_expired(now - t0, h, a, kWaitSum)) {
                             *s_abort = 1;
                             break;
                         }

@@ -339,6 +339,7 @@ struct GangArgs {
     // batch
     int ncls;
     const int *wg_member, *wg_size, *wg_class, *cls_ptr, *order;
+    const int* sys_size;      // workgroups of each system's solve
     int *ticket, *next_sys;
     const int64_t *row_off, *zcol_off, *e_off, *v_off, *w_off;
     const double* x0;

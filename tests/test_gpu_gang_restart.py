@@ -55,22 +55,43 @@ def test_restarts_repeat_bit_for_bit(mesh, s, m, steps):
     assert r <= 1e-8
 
 
-def test_batch_restarts_repeat_bit_for_bit():
-    """Systems of one size: whichever gang takes one, it has the same number of
-    workgroups."""
+# Meshes of 16 to 96 elements: gangs of one to 19 workgroups, and several
+# systems a gang, so which gang takes the last ones depends on the others.
+@pytest.mark.parametrize("ns,lo,hi,m,steps", [(24, 96, 96, 3, 60), (64, 16, 96, 3, 60), (48, 16, 128, 20, 25)])
+def test_batches_repeat_bit_for_bit(ns, lo, hi, m, steps):
     from paper_1906_04051_amd import gmres as G
-    batch = W.make_batch(24, 96, 96, 4)
-    plan, d = G.plan_for(batch, m=3, rtol=0.0, max_iters=60)
+    batch = W.make_batch(ns, lo, hi, 4)
+    plan, d = G.plan_for(batch, m=m, rtol=0.0, max_iters=steps)
     first = None
     for _ in range(REPEATS):
         x, infos = plan.solve_batched(d["b"])
-        assert all(i["iters"] == 60 for i in infos)
+        assert all(i["iters"] == steps for i in infos)
         if first is None:
             first = x.clone()
         assert torch.equal(x, first)
+    assert plan.gang_counts() == dict(gang=REPEATS, given_up=0, other=0)
     plan.close()
     for i, sysm in enumerate(batch.systems):
-        ref = oracle.gmres(sysm, 3, 0.0, 60).x
+        ref = oracle.gmres(sysm, m, 0.0, steps).x
         r = float(np.linalg.norm(first[batch.row_off[i]:batch.row_off[i + 1]].cpu().numpy() - ref)
                   / np.linalg.norm(ref))
         assert r <= 1e-8, (i, r)
+
+
+def test_a_batch_to_tolerance_repeats_bit_for_bit():
+    """Systems that take different numbers of steps, beside a second batch on
+    another stream that changes when gangs become free."""
+    from paper_1906_04051_amd import gmres as G
+    batch = W.make_batch(64, 16, 96, 4)
+    plan, d = G.plan_for(batch, m=30, rtol=1e-10, max_iters=20000)
+    first = plan.solve_batched(d["b"])[0].clone()
+    noise = torch.rand(1 << 24, device="cuda")
+    side = torch.cuda.Stream()
+    for i in range(REPEATS):
+        with torch.cuda.stream(side):
+            for _ in range(3 * i):
+                noise = noise * 1.0000001
+        x, infos = plan.solve_batched(d["b"])
+        assert torch.equal(x, first)
+    torch.cuda.synchronize()
+    plan.close()
