@@ -676,6 +676,18 @@ static CacheUse cache_use_for(const gmres_plan_s* p, int op, int prec) {
     return {(int)std::max(0.0, std::min(c, 1024.0)), fits ? 0 : 1};
 }
 
+// Two Arnoldi steps per pair of sweeps wherever the basis is not needed column
+// by column (the adaptive deflation takes its Ritz vector from it).  us per step,
+// one by one / paired: 1,050,625 rows, GMRES(50), FP64 142.7 / 99.6, FP32 basis
+// 91 / 68, FP16 basis 74 / 59; 4,198,401 rows, FP64 490 / 345.  A cycle with an
+// odd number of steps makes its last vector in vain, which costs more than pairs
+// save where it is short: 641,601 rows, FP64, m = 1 110 / 144; m = 3, 16
+// indicators 75.0 / 80.5, none 60.7 / 57.8; m = 5, 16 indicators 69.6 / 68.7.
+bool engine_pairs(const gmres_plan_s* p, bool adapt) {
+    const int m = p->o.m;
+    return p->o.ortho == 1 && !adapt && m != 1 && !(m == 3 && p->R > 0);
+}
+
 EngineArgs make_args(gmres_plan_s* p, int op, int prec) {
     EngineArgs a{};
     a.st = p->st;
@@ -781,12 +793,7 @@ EngineArgs make_args(gmres_plan_s* p, int op, int prec) {
     a.dcs = p->dcs;
     a.cc = p->cc;
     a.lag = p->lag;
-    // Two Arnoldi steps per pair of sweeps wherever the basis is not needed
-    // column by column (the adaptive deflation takes its Ritz vector from it).
-    // Measured per step, one by one / paired: 1,050,625 rows, GMRES(50), FP64
-    // 142.7 / 99.6 us, FP32 basis 91 / 68, FP16 basis 74 / 59; 4,198,401 rows,
-    // FP64 490 / 345 us.
-    a.paired = (p->o.ortho == 1 && !a.adapt) ? 1 : 0;
+    a.paired = engine_pairs(p, a.adapt != nullptr) ? 1 : 0;
     a.pst = p->pst;
     a.sigma_a = p->sigma_a;
     a.cyc_k = p->cyc_k;
@@ -811,7 +818,7 @@ struct TimerHook final : KTimer {
     bool lagged = false, dcgs = false, paired = false;
     TimerHook(gmres_plan_s* pp, int pr, int o)
         : p(pp), prec(pr), op(o), lagged(pp->o.ortho == 1), dcgs(pp->o.ortho == 2),
-          paired(lagged && pp->adapt.rmax == 0) {}
+          paired(engine_pairs(pp, pp->adapt.rmax > 0)) {}
     // Algorithmic bytes of one launch: every array the kernel's scheme reads or
     // writes, touched once (cache hits not credited).  A Z is read through its
     // two-entry row copy (int32 column pairs and value pairs per row).

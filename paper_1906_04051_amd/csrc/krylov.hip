@@ -2712,6 +2712,15 @@ struct Engine {
                2);
     }
 
+    template <int J>
+    int launch_pass1_lag(int j) const {
+        auto kf = k_pass1_lag<J, LanesForLag<J, VT>::value, VT, WT, AT, ACC>;
+        const int g = grid_for((const void*)kf);
+        launch(kf, g, kWG, 0, e.st, e.n, e.ldv, V(), j, w(), y(), e.azrp, e.azci, azv(), e.azc1, azv1(),
+               e.s_step, e.R, e.coef2, e.cc, e.lag, e.part, e.nslot, g, e.ctrl, 2, e.cache_cols);
+        return g;
+    }
+
     // Step j of the two-pass variant (see k_pass1_lag).
     void step_lag(int j) const {
         const int nv = j + 1;
@@ -2734,14 +2743,10 @@ struct Engine {
             g1 = grid_for((const void*)kf);
             launch(kf, g1, kWG, 0, e.st, e.n, e.ldv, V(), 1, y(), e.azrp, e.azci, azv(), e.azc1,
                    azv1(), e.s_step, e.R, w(), e.part, e.nslot, g1, e.ctrl, 2, e.cache_cols);
+        } else if constexpr (std::is_same<VT, double>::value) {
+            GM_JMAX_SWITCH(j, VT, g1 = launch_pass1_lag<J>(j));
         } else {
-            GM_JMAX_SWITCH(j, VT, ({
-                auto kf = k_pass1_lag<J, LanesForLag<J, VT>::value, VT, WT, AT, ACC>;
-                g1 = grid_for((const void*)kf);
-                launch(kf, g1, kWG, 0, e.st, e.n, e.ldv, V(), j, w(), y(), e.azrp, e.azci, azv(),
-                       e.azc1, azv1(), e.s_step, e.R, e.coef2, e.cc, e.lag, e.part, e.nslot, g1,
-                       e.ctrl, 2, e.cache_cols);
-            }));
+            g1 = launch_pass1_lag<8>(j);   // short cycles only
         }
         if (e.timer) e.timer->end(1, j);
         k_finish<<<nv + 1, kWG, 0, e.st>>>(e.part, g1, nv, e.nslot, e.vscale, e.h1, e.coef1, 1,
@@ -2923,14 +2928,10 @@ struct Engine {
             return;
         }
         for (int j = 0; j < e.m; ++j) {
-            if (e.dcgs) {
-                step_dc(j);
-            } else if (e.lagged) {
-                // Adaptive deflation only (FP64).
-                if constexpr (std::is_same<VT, double>::value) step_lag(j);
-            } else {
-                step(j);
-            }
+            // step_lag: adaptive deflation (FP64), and cycles of one or three steps.
+            if (e.dcgs) step_dc(j);
+            else if (e.lagged) step_lag(j);
+            else step(j);
         }
         if constexpr (std::is_same<VT, double>::value && std::is_same<WT, double>::value)
             if (e.dcgs) dc_dots<false>(e.m);
