@@ -34,17 +34,23 @@ METRIC = "time-to-rtol 1e-8 (s) + SpMV/Arnoldi HBM GB/s; mixed vs FP64 GMRES"
 HBM_PEAK_GBS = 8000.0
 
 # HBM traffic of the dominant kernel per workload (FP64 first Gram-Schmidt
-# sweep of the two-sweep variant over a restart cycle of GMRES(50)) from
+# sweep of a pair of steps, k_pair1, over a restart cycle of GMRES(50)) from
 # FETCH_SIZE and WRITE_SIZE counter runs of `bench.py --pmc-sample`, each
 # scaled by what the same counter reads for a 512 MiB device copy.  Valid only
 # while the kernel sources hash to `sources_sha256`; None until measured.
 TRAFFIC = {
     5: {"kind": "pass1_lag",
-        "sources_sha256": "c25a2e2286a92d6786a47946ce0578b3f3cc6d7c1974981fab29dd4787a827c1",
-        "bytes_per_launch": 1076.4e6},   # 1,008.6 MB read + 67.8 MB written (98 launches)
+        "sources_sha256": "6a53322ea6b92eb3f06451da17280f86e98051386cb1bf7892f88f52ba014af9",
+        "bytes_per_launch": 1144.7e6},   # 1,042.5 MB read + 102.2 MB written (48 launches)
 }
 KERNEL_SOURCES = ("paper_1906_04051_amd/csrc/krylov.hip", "paper_1906_04051_amd/csrc/common.hpp",
                   "paper_1906_04051_amd/csrc/internal.hpp")
+
+
+def hip_kernel(cls, ortho):
+    """HIP kernel behind a sweep class of a solve by pairs of steps (None for
+    the others)."""
+    return {"pass1": "k_pair1", "pass1_lag": "k_pair1", "pass2": "k_pair2"}.get(cls) if ortho == 1 else None
 
 
 def kernel_sources_sha256():
@@ -595,7 +601,8 @@ def single_config(args):
         out["roofline"] = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                            "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                            "traffic_unit": "bytes/launch",
-                           "kernel": f"{src}.{dom}", "launches": int(v["launches"]),
+                           "kernel": f"{src}.{dom}", "hip_kernel": hip_kernel(dom, args.ortho),
+                           "launches": int(v["launches"]),
                            "avg_launch_us": 1000 * v["ms"] / v["launches"],
                            "bytes_per_launch_avg": v["bytes"] / v["launches"]}
         # A measured ceiling beside the published peak (outside the timed steps).

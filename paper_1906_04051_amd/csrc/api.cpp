@@ -1971,7 +1971,7 @@ static void drop_graphs(gmres_plan_s* p) {
 // (mesh width).  Kept (gang_nwg > 0) where its estimate beats one workgroup
 // per system: a system-step takes about 18 ns a row there, with at most one
 // per compute unit in flight; in a gang about 6 us plus 30 ns for each row of
-// a workgroup (96 systems of 289 to 9,409 rows: 172 -> 26 ms; a chip-filling
+// a workgroup (96 systems of 289 to 9,409 rows: 178 -> 30 ms; a chip-filling
 // batch stays where it was, its rows cost half as much without rendezvous).
 static gmres_status plan_batch_gangs(gmres_plan_s* p) {
     p->gang_nwg = 0;

@@ -2,7 +2,7 @@
 //
 // A gang of K workgroups (one per compute unit, all on the chip together) owns
 // a system: workgroup `me` owns a contiguous range of RW sliced
-// positions, one thread per row.  The Krylov basis of those rows lives in the
+// positions, one to four rows a thread.  The Krylov basis of those rows lives in the
 // workgroup's LDS (columns that do not fit there in global memory, read only
 // by their owner), so the two Gram-Schmidt sweeps of a step touch no HBM.
 // The arithmetic is the two-sweep CGS2 with lagged normalisation of
@@ -11,10 +11,12 @@
 // decisions are computed redundantly by every workgroup from the same sums in
 // the same order, so no workgroup waits for a serial kernel.
 //
-// Why: below about 300,000 rows a step of the kernel-per-phase engine is seven
-// dependent launches of 4-10 us each, whatever the size (64 x 64 Q1: 35 us,
-// 256 x 256: 44 us a step, against under 2 us of memory traffic).  Here a step
-// is three rendezvous of the gang (two without a deflation basis).
+// Why: below about 300,000 rows two steps of the kernel-per-phase engine are a
+// dozen dependent launches of 4-10 us each, whatever the size, against a few us
+// of memory traffic.  Here a step is three rendezvous of the gang (two without
+// a deflation basis).  us per step, gang / engine: 4,225 rows, 16 columns, m =
+// 30, 12.6 / 27.3; 30,276 rows, no columns, 9.6 / 18.3; 66,049 rows, 64 columns,
+// m = 50, 19.1 / 32.9; where the engine wins, see gang_basis_limit.
 //
 // Rendezvous: each workgroup stores its epoch in its own flag word and polls
 // all K words (one coalesced load per try); no read-modify-write, no central
@@ -43,11 +45,11 @@
 // restart and its update needs the basis, so a launch runs one cycle.  Within
 // it U^T x rides on the exchange that already carries the second projection's
 // sums (no further rendezvous) and A U C U^T x is added behind the SpMV; the
-// basis goes to memory once, at the end, for the Ritz step's kernels.  Bratu
-// 20^3 (Newton, 350 steps of m = 50): 21 us a step, 50 on the per-phase engine;
-// a whole Newton solve 21.2 -> 12.3 ms.  66,049 rows, m = 50, 8 cycles of up to
-// 22 columns: 32 us a step, Ritz steps included, 67 on the per-phase engine;
-// 361,201 rows, m = 30: 63 / 101.
+// basis goes to memory once, at the end, for the Ritz step's kernels.  Ritz
+// steps included, gang / engine (one step per pair of sweeps there): a Newton
+// solve of Bratu 20^3 (about 263 steps, m = 50) 8.8 / 18.0 ms; 66,049 rows, m =
+// 50, up to 22 columns, 30 cycles: 25.8 / 57.7 us a step; 361,201 rows, m = 30,
+// 8 cycles: 47.6 / 76.4.
 #include "internal.hpp"
 
 #include <chrono>
