@@ -260,6 +260,13 @@ int default_lanes(int64_t n, int64_t nnz, bool have_sell, int64_t sell_total) {
     return rho <= 40 ? 4 : 32;
 }
 
+// The variant of op (1: A^T).  A^T can lack the sliced-ELL copy that A has: where
+// A's rows are of one length and its columns are not, only the copy of A^T is
+// past its budget.  Its rows are then read from the CSR copy.
+int lanes_for(const gmres_plan_s* p, int op) {
+    return op == 1 && p->L == kSell && !p->tsell_col ? default_lanes(p->n, p->nnz, false, 0) : p->L;
+}
+
 int max_row_len(hipStream_t st, int64_t n, const int* rp, int* d_tmp) {
     return zt_max_row(st, (int)n, rp, d_tmp);
 }
@@ -694,7 +701,7 @@ EngineArgs make_args(gmres_plan_s* p, int op, int prec) {
     a.prec = prec;
     a.n = (int)p->n;
     a.nscale = std::sqrt((double)p->n);
-    a.L = p->L;
+    a.L = lanes_for(p, op);
     a.NB = p->NB;
     a.nbcap = p->NB_cap;
     a.pass_grid = 1;
@@ -734,7 +741,7 @@ EngineArgs make_args(gmres_plan_s* p, int op, int prec) {
     a.ztv = p->ztv;
     a.tpart = p->tpart;
     a.Einv = p->Einv;
-    const int rb = (p->L == kSell || p->L == -256) ? 256 : (p->L == -128 ? 128 : 0);
+    const int rb = (a.L == kSell || a.L == -256) ? 256 : (a.L == -128 ? 128 : 0);
     a.fuse_rb = (p->R > 0 && rb != 0 && rb == p->slots_rb) ? rb : 0;
     if (op == 0) {
         a.sell_off = p->sell_off;
